@@ -1,7 +1,7 @@
 // Embedding backward without atomics, for callers that know the indices before the gradient
 // arrives (the paper computes its index tensors once per mini-batch, Section IV-B-2, and
 // names the colliding additions of Section IV-C-3 as the cost of this step): the token
-// positions are ordered by index once (a stable radix sort, a call of its own), and the
+// positions are ordered by index once (position_sort_kernels.h, a call of its own), and the
 // gradient rows of an index are then summed in fp32 in that order and written as ONE row.
 //
 // The sorted positions are cut into chunks of 256 entries, one workgroup each.  A workgroup
@@ -30,27 +30,14 @@ struct EmbChunkInfo {
 
 struct EmbSortedArgs {
   const uint32_t* dy;     // [rows, pairs] packed pairs of 16-bit values
-  const uint32_t* keys;   // [rows] sorted: index, or vocab for entries that are skipped (sorted last)
-  const uint32_t* order;  // [rows] token position of each sorted entry
+  const uint2* sorted;    // [rows] {index, or vocab for entries that are skipped (sorted last); token position}
   EmbChunkInfo* info;     // [chunks]
   float* partial;         // [chunks][2][2 * pairs]: head and tail partial sums
   uint32_t* dw;           // [vocab, pairs]
   int32_t rows, pairs, vocab;
-  int32_t accumulate;     // 1: add onto the weight rows that are there, 0: they are known to be zero
+  int32_t accumulate;     // 1: add onto the weight rows that are there, 0: they count as zero
+  int32_t clear;          // workgroups of the chunk kernel that clear the rows nothing is added onto (0 if accumulate)
 };
-
-// keys[t] = indices[t] if the token counts (in range, not the padding index, t < *n_rows), else vocab
-__global__ __launch_bounds__(256) void emb_keys_kernel(const int32_t* __restrict__ indices, const int32_t* __restrict__ n_rows,
-                                                       int rows, int vocab, int padding_idx, uint32_t* __restrict__ keys,
-                                                       uint32_t* __restrict__ positions) {
-  int n = rows;
-  if (n_rows) n = min(max(*n_rows, 0), rows);
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < rows; t += gridDim.x * blockDim.x) {
-    const int v = t < n ? indices[t] : -1;
-    keys[t] = (v >= 0 && v < vocab && v != padding_idx) ? (uint32_t)v : (uint32_t)vocab;
-    positions[t] = (uint32_t)t;
-  }
-}
 
 // x (eight 16-bit values in four dwords) added onto eight fp32 sums
 template <bool BF16>
@@ -86,6 +73,36 @@ static __device__ __forceinline__ uint4 emb_finish8(const uint4& old, float (&s)
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Weight rows first .. first + kEmbClearRows - 1 that no sorted entry names <- zeros (the others
+// are written whole by their one writer, so clearing all of them ahead of the sums would move
+// most of dw twice and cost a launch: 9 us for 30522 x 768 weights).  A thread looks its row up
+// in the sorted entries by bisection; these workgroups come first in the grid, so that their
+// chains of loads run beside the sums.
+constexpr int kEmbClearRows = 64;
+static __device__ void emb_clear_rows(const EmbSortedArgs& a, int first, uint32_t* s_absent) {
+  const int tid = threadIdx.x, n = min(kEmbClearRows, a.vocab - first);
+  if (tid < n) {
+    const uint32_t row = (uint32_t)(first + tid);
+    int lo = 0, hi = a.rows;  // first entry whose index is not below `row`
+    while (lo < hi) {
+      const int mid = lo + ((hi - lo) >> 1);
+      if (a.sorted[mid].x < row)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    s_absent[tid] = lo == a.rows || a.sorted[lo].x != row;
+  }
+  __syncthreads();
+  const int pieces = a.pairs >> 2;  // of 16 bytes
+  for (int r = 0; r < n; r++) {
+    if (!s_absent[r]) continue;  // uniform
+    uint4* w = reinterpret_cast<uint4*>(a.dw) + (int64_t)(first + r) * pieces;
+    for (int i = tid; i < pieces; i += kEmbSortThreads) w[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  __syncthreads();  // s_absent may be written again
+}
+
 constexpr int kEmbAhead = 16;  // rows a thread has in flight
 
 // One workgroup per chunk of `chunk` (<= kEmbChunk) sorted entries; thread i owns the columns
@@ -97,12 +114,18 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
   __shared__ uint32_t s_code[kEmbChunk];  // index * 4 + {0: the run goes on, 1: head partial, 2: tail partial, 3: final row}
   __shared__ uint32_t s_pos[kEmbChunk];
   __shared__ int s_live;                  // entries of the chunk that count (skipped ones are sorted last)
-  const int c = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < a.clear) {
+    for (int64_t first = (int64_t)blockIdx.x * kEmbClearRows; first < a.vocab; first += (int64_t)a.clear * kEmbClearRows)
+      emb_clear_rows(a, (int)first, s_pos);
+    return;
+  }
+  const int c = blockIdx.x - a.clear;
   const int base = c * chunk;
   const int n = min(chunk, a.rows - base);
   const uint32_t none = (uint32_t)a.vocab;
-  const uint32_t first = a.keys[base], last = a.keys[base + n - 1];
-  const uint32_t before = base > 0 ? a.keys[base - 1] : none, after = base + n < a.rows ? a.keys[base + n] : none;
+  const uint32_t first = a.sorted[base].x, last = a.sorted[base + n - 1].x;
+  const uint32_t before = base > 0 ? a.sorted[base - 1].x : none, after = base + n < a.rows ? a.sorted[base + n].x : none;
   const bool head = first != none && before == first;  // the first run began before this chunk
   const bool tail = last != none && after == last;     // the last run goes on after it
   if (tid == 0) {
@@ -116,8 +139,9 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
   }
   __syncthreads();
   for (int r = tid; r < n; r += kEmbSortThreads) {
-    const uint32_t key = a.keys[base + r];
-    const uint32_t next = r + 1 < n ? a.keys[base + r + 1] : after;
+    const uint2 entry = a.sorted[base + r];
+    const uint32_t key = entry.x;
+    const uint32_t next = r + 1 < n ? a.sorted[base + r + 1].x : after;
     uint32_t action = 0;
     if (key != none && (r == n - 1 || next != key)) {  // the run ends here, or leaves the chunk
       if (head && key == first)
@@ -128,7 +152,7 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
         action = 3;
     }
     s_code[r] = key * 4u + action;
-    s_pos[r] = a.order[base + r];
+    s_pos[r] = entry.y;
     if (key != none && (r == n - 1 || next == none)) s_live = r + 1;  // exactly one entry qualifies
   }
   __syncthreads();
@@ -170,8 +194,10 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
 // One workgroup per chunk in which a run begins that goes on into later chunks: its partial
 // sums are added in chunk order and the row is written.  Where the run ends is found first (a
 // binary search in the sorted indices by one thread), so that the partial sums - up to a few
-// hundred for the most frequent index of a large batch - can then be fetched four at a time
-// instead of one after the other.
+// hundred for the most frequent index of a large batch, and its one workgroup is what the
+// kernel waits for - can then be fetched kEmbCombineAhead at a time and added in order
+// (527340 Zipf-distributed rows of 768: 60 us with four at a time, 22 with sixteen).
+constexpr int kEmbCombineAhead = 16;
 template <bool BF16>
 __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbSortedArgs a, const int chunk) {
   __shared__ int s_last;
@@ -182,7 +208,7 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbS
     int lo = (c + 1) * chunk, hi = a.rows;  // first position after the run: keys[lo - 1] == key < keys[hi] (or hi == rows)
     while (lo < hi) {
       const int mid = lo + ((hi - lo) >> 1);
-      if (a.keys[mid] <= (uint32_t)key)
+      if (a.sorted[mid].x <= (uint32_t)key)
         lo = mid + 1;
       else
         hi = mid;
@@ -196,19 +222,20 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbS
   for (int col = 8 * threadIdx.x; col < hidden; col += 8 * kEmbSortThreads) {
     const float4* p = reinterpret_cast<const float4*>(a.partial + ((int64_t)c * 2 + 1) * hidden + col);
     float s[8] = {p[0].x, p[0].y, p[0].z, p[0].w, p[1].x, p[1].y, p[1].z, p[1].w};
-    for (int d0 = c + 1; d0 <= d_last; d0 += 4) {
-      float4 t[4][2];
+    for (int d0 = c + 1; d0 <= d_last; d0 += kEmbCombineAhead) {
+      float4 t[kEmbCombineAhead][2];
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
+      for (int u = 0; u < kEmbCombineAhead; u++) {
         const float4* q = reinterpret_cast<const float4*>(a.partial + (int64_t)min(d0 + u, d_last) * 2 * hidden + col);
         t[u][0] = q[0];
         t[u][1] = q[1];
       }
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
-        if (d0 + u > d_last) break;
-        s[0] += t[u][0].x, s[1] += t[u][0].y, s[2] += t[u][0].z, s[3] += t[u][0].w;
-        s[4] += t[u][1].x, s[5] += t[u][1].y, s[6] += t[u][1].z, s[7] += t[u][1].w;
+      for (int u = 0; u < kEmbCombineAhead; u++) {
+        if (d0 + u <= d_last) {
+          s[0] += t[u][0].x, s[1] += t[u][0].y, s[2] += t[u][0].z, s[3] += t[u][0].w;
+          s[4] += t[u][1].x, s[5] += t[u][1].y, s[6] += t[u][1].z, s[7] += t[u][1].w;
+        }
       }
     }
     uint4* w = reinterpret_cast<uint4*>(dw + (int64_t)key * hidden + col);

@@ -152,6 +152,23 @@ def test_sorted_variant_bit_for_bit_and_repeatable(t, n, vocab, init, dtype):
     assert np.array_equal(results[0], want)
 
 
+@pytest.mark.parametrize("t", [1, 64, 1024, 1025, 4096, 4097, 10240, 65536, 65537])
+@pytest.mark.parametrize("vocab", [1, 255, 300, 70000])
+def test_sorted_variant_at_the_edges_of_the_sort(t, vocab):
+    """One workgroup up to 4096 entries (256 threads up to 1024), tiles of 2048 from there on, another launch from 32 tiles
+    on; one, two and three digits.  The order shows in the rounding of the sums: bit for bit."""
+    rng = np.random.default_rng(t + vocab)
+    dy_bits = wl.to_bits(rng.standard_normal((t, 8)).astype(np.float32), "f16")
+    ids = rng.integers(-1, vocab + 1, t).astype(np.int32)   # with some out of range on both sides
+    ids[rng.random(t) < 0.2] = vocab - 1
+    ws = torch.empty(fmha.fmha_embedding_sort_workspace_size(t, 8), dtype=torch.uint8, device="cuda")
+    fmha.fmha_embedding_sort(torch.from_numpy(ids).cuda(), 8, vocab, ws)
+    dw = torch.full((vocab, 8), float("nan"), dtype=torch.float16, device="cuda")
+    fmha.fmha_embedding_bwd_sorted(to_dev(dy_bits, "f16"), ws, dw, zero_first=True)
+    got = dw.view(torch.int16).cpu().numpy().view(np.uint16)
+    assert np.array_equal(got, sorted_order_reference(dy_bits, ids, vocab, "f16", 32))
+
+
 def test_embedding_bwd_argument_errors():
     dy = torch.zeros((4, 12), dtype=torch.float16, device="cuda")
     idx = torch.zeros(4, dtype=torch.int32, device="cuda")
