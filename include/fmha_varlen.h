@@ -219,7 +219,7 @@ int fmha_unpad_indices_host(const int32_t* input_mask, int32_t batch, int32_t se
                             int32_t* max_seqlen);
 
 /* The same on the device: all arrays are device memory (inverse may be NULL), sizes as
- * above; three small launches on `stream`, no host synchronisation.  Entries of
+ * above; one to three small launches on `stream`, no host synchronisation.  Entries of
  * nonzero_indices at and beyond cu_seqlens[batch] are left alone. */
 int fmha_unpad_indices(const int32_t* input_mask, int32_t batch, int32_t seqlen,
                        int32_t* nonzero_indices, int32_t* inverse, int32_t* cu_seqlens,

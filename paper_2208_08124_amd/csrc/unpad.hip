@@ -31,6 +31,12 @@ int check_rows(const void* src, const void* dst, const int32_t* map, const int32
   return FMHA_OK;
 }
 
+// Where unpad_indices takes one launch instead of three (mask_all_kernel): a bound on what the
+// last row's workgroup reads, and one on what all of them read together (half of it).  us with
+// three launches / with one: 56 x 512 9.0 / 3.9, 256 x 256 7.8 / 5.3, 128 x 1024 11.9 / 7.1 (both
+// bounds reached); beyond, 512 x 128 7.1 / 6.7, 1024 x 32 6.9 / 8.1, 1024 x 128 7.2 / 14.8.
+constexpr int64_t kMaskAllEntries = 131072, kMaskAllReads = (int64_t)1 << 24;
+
 unsigned copy_grid(int64_t rows, int64_t chunks) {
   const int64_t want = (rows * chunks + 1023) / 1024;  // four pieces per thread and trip
   const int64_t cap = 256 * 16;  // 16 workgroups per compute unit keep every memory channel busy
@@ -81,6 +87,11 @@ int fmha_unpad_indices(const int32_t* input_mask, int32_t batch, int32_t seqlen,
   if (batch == 0) {  // only cu[0] = 0 to write
     fmha::prefix_sum_kernel<<<1, fmha::kScanThreads, 0, st>>>(cu_seqlens, 0);
     return launched("prefix sum");
+  }
+  const int64_t entries = (int64_t)batch * seqlen;
+  if (entries <= kMaskAllEntries && entries * batch <= kMaskAllReads) {
+    fmha::mask_all_kernel<<<(unsigned)batch, fmha::kMaskAllThreads, 0, st>>>(input_mask, batch, seqlen, cu_seqlens, nonzero_indices, inverse);
+    return launched("mask");
   }
   fmha::mask_count_kernel<<<grid, fmha::kUnpadThreads, 0, st>>>(input_mask, batch, seqlen, cu_seqlens);
   if ((rc = launched("mask count"))) return rc;
