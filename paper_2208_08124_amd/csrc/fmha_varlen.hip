@@ -365,8 +365,15 @@ int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   if (p->batch == 0 || p->total_tokens == 0) return FMHA_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   Workspace w = carve(p->workspace, p->batch, p->total_tokens, p->heads);
-  if ((rc = launch_schedule(p, w, st))) return rc;
+  // Small batches work out the tile list in the forward kernel (SELF): one lane per sequence,
+  // and every item resident from the start (4 workgroups per compute unit), where the list's
+  // order does not matter.
+  const bool self = da.thr == 0 && !(p->flags & FMHA_FLAG_REUSE_SCHEDULE) && p->batch <= fmha::kSelfListBatch &&
+                    items_bound(p) <= (int64_t)compute_units() * 4;
+  if (!self && (rc = launch_schedule(p, w, st))) return rc;
   a.pb = problem_of(p, w);
+  a.list = fmha::ListArgs{p->cu_seqlens, p->seqused, p->batch, (int32_t)tile_capacity(p->batch, p->total_tokens),
+                          w.count, w.list};
   a.feed = fmha::FeedArgs{w.feed, 1};
   a.q = static_cast<const uint16_t*>(q);
   a.k = static_cast<const uint16_t*>(k);
@@ -376,13 +383,19 @@ int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   const unsigned grid = grid_for(p, 3);
   a.drop = da;
   // p = 0 (threshold 0) keeps everything: the plain kernels serve it
-  if (da.thr == 0) {
+  if (self) {
+    const unsigned grid_self = (unsigned)items_bound(p) + 1;  // one writes the list
+    if (p->dtype == FMHA_F16)
+      fmha::fmha_fwd64_kernel<_Float16, true><<<grid_self, fmha::kF64Threads, 0, st>>>(a);
+    else
+      fmha::fmha_fwd64_kernel<__bf16, true><<<grid_self, fmha::kF64Threads, 0, st>>>(a);
+  } else if (da.thr == 0) {
     // persistent: 4 workgroups of 2 wavefronts per compute unit
     const unsigned grid64 = feed_grid(p, 4, w, &a.feed);
     if (p->dtype == FMHA_F16)
-      fmha::fmha_fwd64_kernel<_Float16><<<grid64, fmha::kF64Threads, 0, st>>>(a);
+      fmha::fmha_fwd64_kernel<_Float16, false><<<grid64, fmha::kF64Threads, 0, st>>>(a);
     else
-      fmha::fmha_fwd64_kernel<__bf16><<<grid64, fmha::kF64Threads, 0, st>>>(a);
+      fmha::fmha_fwd64_kernel<__bf16, false><<<grid64, fmha::kF64Threads, 0, st>>>(a);
   } else {
     if (p->dtype == FMHA_F16)
       fmha::fmha_fwd_kernel<_Float16, true><<<grid, fmha::kThreads, 0, st>>>(a);

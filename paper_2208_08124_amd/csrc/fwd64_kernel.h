@@ -36,6 +36,7 @@
 #include "item_feed.h"
 #include "kernel_args.h"
 #include "mfma_tiles.h"
+#include "schedule.h"
 
 namespace fmha {
 
@@ -265,13 +266,74 @@ struct Fwd64Item {
   int n, n_full;  // steps of 32 keys; complete tiles
 };
 
-template <typename T>
+constexpr int kSelfListBatch = 64;  // sequences of a batch whose tile list the forward works out itself
+
+// Small batches (SELF): lane i holds sequence i and where its tiles begin, in pack order.
+struct SelfList {
+  SchedSeq seq;
+  int tiles, first;  // of this lane's sequence
+  int total;         // of the batch
+
+  __device__ __forceinline__ void build(const ListArgs& a, int total_tokens) {
+    const int lane = lane_id();
+    seq = SchedSeq{0, 0, 0};
+    if (lane < a.batch) seq = sched_seq(a.cu, a.seqused, lane, total_tokens);
+    tiles = seq.len <= 0 ? 0 : (seq.len + kTileRows - 1) / kTileRows;
+    int incl = tiles;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += up;
+    }
+    first = incl - tiles;
+    total = min(__builtin_amdgcn_readlane(incl, 63), a.cap);
+  }
+  // Tile i (< total; uniform over the wavefront).
+  __device__ __forceinline__ TileItem tile(int i) const {
+    const uint64_t owner = __ballot(first <= i && i < first + tiles);
+    const int l = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(owner));
+    return TileItem{__builtin_amdgcn_readlane(seq.r0, l), __builtin_amdgcn_readlane(seq.len, l),
+                    __builtin_amdgcn_readlane(seq.nk, l), (i - __builtin_amdgcn_readlane(first, l)) * kTileRows};
+  }
+  // One wavefront: the list as the tile-list kernel leaves it, longest sequences first.
+  __device__ __forceinline__ void publish(const ListArgs& a) const {
+    const int lane = lane_id();
+    const int bucket = sched_bucket(seq.nk);
+    int at = 0;
+    for (int i = 0; i < a.batch; i++) {  // uniform
+      const int bi = __builtin_amdgcn_readlane(bucket, i), ti = __builtin_amdgcn_readlane(tiles, i);
+      if (bi < bucket || (bi == bucket && i < lane)) at += ti;
+    }
+    for (int t = 0; t < tiles; t++)
+      if (at + t < a.cap) a.list[at + t] = TileItem{seq.r0, seq.len, seq.nk, t * kTileRows};
+    if (lane == 0) *a.count = total;
+  }
+};
+
+// SELF: for batches so small that every (tile, head) has a workgroup of its own and the time
+// is the chain of launches and memory round trips.  The workgroups work out the tile list
+// themselves, from the prefix sums and in pack order (with everything running at once the
+// order is of no account), instead of waiting for a launch that does; the last workgroup
+// takes no item and leaves the list and the feed's counters in the workspace for a backward
+// call.  Measured, a call among others: four sequences of 3 .. 128 tokens, two heads, 12.3 us
+// with two launches and 9.7 with one; nine of up to 387 tokens, twelve heads, 14.2 and 11.5.
+template <typename T, bool SELF>
 __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArgs a) {
   __shared__ __align__(1024) Fwd64Lds lds;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (tells the compiler it is uniform)
   const int heads = a.pb.heads;
-  const int n_items = tile_count(a.pb) * heads;
+  SelfList self;
+  if (SELF) {
+    self.build(a.list, a.pb.total_tokens);
+    if (blockIdx.x == gridDim.x - 1) {
+      for (int i = threadIdx.x; i < kFeedWords; i += kF64Threads) a.feed.counters[i] = 0u;
+      if (wave == 0) self.publish(a.list);
+      return;
+    }
+  }
+  const int n_items = (SELF ? self.total : tile_count(a.pb)) * heads;
+  auto tile_of = [&](int i) { return SELF ? self.tile(i) : load_tile(a.pb, i); };
   const float c2 = fabsf(a.pb.scale) * kLog2e;  // scores are kept in the log2 domain
   const uint32_t k_addr = lds_addr(&lds.k[0][0]), v_addr = lds_addr(&lds.v[0][0]);
   constexpr uint32_t kTileBytes = kTile32 * 2;
@@ -505,16 +567,18 @@ __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArg
     return __builtin_amdgcn_ballot_w64(!(fabsf(lsum) < 3.0e38f)) == 0;
   };
 
-  // persistent workgroups; the item feed hands out the (tile, head) items, two ahead
+  // persistent workgroups; the item feed hands out the (tile, head) items, two ahead (SELF: a
+  // second item only if max_seqlen was stated too small and there are more than expected)
   ItemFeed feed;
-  int item = feed.init(a.feed, blockIdx.x, gridDim.x);
+  const int self_step = gridDim.x - 1;
+  int item = SELF ? (int)blockIdx.x : feed.init(a.feed, blockIdx.x, gridDim.x);
   if (item >= n_items) {
-    feed.finish(a.feed, gridDim.x);
+    if (!SELF) feed.finish(a.feed, gridDim.x);
     return;
   }
-  int item1 = feed.next();
-  Fwd64Item cur = decode(load_tile(a.pb, item / heads), item);
-  TileItem ti1 = load_tile(a.pb, (item1 < n_items ? item1 : item) / heads);
+  int item1 = SELF ? item + self_step : feed.next();
+  Fwd64Item cur = decode(tile_of(item / heads), item);
+  TileItem ti1 = tile_of((item1 < n_items ? item1 : item) / heads);
   int vb = 0, parity = 0;
   request_q(cur, st.q);
   request_kv(cur, vb);
@@ -530,10 +594,10 @@ __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArg
     // everybody.  (The words are rewritten an item later at the earliest, with other
     // barriers in between; the mailbox words are used in turn on top of that.)
     if ((threadIdx.x & 63) == 0) lds.redo[wave] = fine ? 0u : 1u;
-    feed.publish(&lds.mailbox[parity]);
+    if (!SELF) feed.publish(&lds.mailbox[parity]);
     pair_barrier();
     const bool redo = __builtin_amdgcn_readfirstlane((int)(lds.redo[0] | lds.redo[1])) != 0;
-    feed.receive(&lds.mailbox[parity]);
+    if (!SELF) feed.receive(&lds.mailbox[parity]);
     parity ^= 1;
     if (redo) {
       request_kv(cur, vb_next);
@@ -542,9 +606,9 @@ __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArg
     }
 
     // the item after the next one: its record is fetched now and used an item later
-    const int item2 = feed.next();
-    feed.request(a.feed);  // answered long before the end of the next item
-    const TileItem ti2 = load_tile(a.pb, (item2 < n_items ? item2 : item) / heads);
+    const int item2 = SELF ? item1 + self_step : feed.next();
+    if (!SELF) feed.request(a.feed);  // answered long before the end of the next item
+    const TileItem ti2 = tile_of((item2 < n_items ? item2 : item) / heads);
 
     // The next item's first transfers go out before this item's results are stored.  Both
     // wavefronts are past the barriers above, so all K slots are free; V(0) of the next item
@@ -585,7 +649,7 @@ __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArg
     item1 = item2;
     ti1 = ti2;
   }
-  feed.finish(a.feed, gridDim.x);
+  if (!SELF) feed.finish(a.feed, gridDim.x);
 }
 
 }  // namespace fmha

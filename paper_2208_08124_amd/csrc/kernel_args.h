@@ -36,8 +36,18 @@ struct DropArgs {
   float rp;         // 256 / (256 - thr), multiplies what is kept
 };
 
+// What the forward of a small batch needs to work out the tile list itself (fwd64_kernel.h).
+struct ListArgs {
+  const int32_t* cu;       // [batch + 1]
+  const int32_t* seqused;  // [batch] or null
+  int32_t batch, cap;      // at most 64 sequences; room in the list
+  int32_t* count;          // the list is still left in the workspace, for the backward
+  TileItem* list;
+};
+
 struct FwdArgs {
   Problem pb;
+  ListArgs list;
   DropArgs drop;
   FeedArgs feed;
   const uint16_t *q, *k, *v;

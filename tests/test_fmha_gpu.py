@@ -115,6 +115,51 @@ def test_schedule_covers_every_tile_once_longest_first():
     assert (np.diff(bucket) <= 0).all(), "tiles are not ordered longest sequence first"
 
 
+@pytest.mark.parametrize("lengths,heads,max_seqlen,used", [
+    ([1], 1, 0, False),
+    ([0, 0, 7, 0], 2, 0, False),
+    ([5, 0, 130, 64, 0], 3, 130, True),
+    (list(range(1, 65)), 2, 64, False),             # 64 sequences: one lane each
+    (list(range(1, 66)), 2, 65, False),             # 65: the tile-list kernel
+    ([128] * 63 + [100], 16, 128, False),           # 1024 items: a workgroup each
+    ([512, 300, 700], 4, 1, False),                 # more items than max_seqlen lets expect
+])
+def test_small_batches_find_their_tiles_in_the_forward(lengths, heads, max_seqlen, used):
+    """The forward of a small batch works out the tile list itself, and leaves it for others: a
+    second forward that only reads the list gives the same bits, and the backward is right."""
+    b = wl.make_batch(lengths, heads, "bf16", seed=31 + len(lengths))
+    if used:
+        b["seqused"] = np.array([min(x, 40) for x in lengths], dtype=np.int32)
+    b["max_seqlen"] = max_seqlen
+    d = DeviceBatch(b, True)
+    d.ws.fill_(0x5a)   # whatever the workspace held before
+    d.fwd()
+    o, lse = d.o.clone(), d.lse.clone()
+    _, c_off, l_off = fmha.fmha_varlen_schedule_info(b["batch"], b["total_tokens"])
+    if b["total_tokens"]:
+        ws = d.ws.cpu().numpy()
+        n = int(ws[c_off:c_off + 4].view(np.int32)[0])
+        items = ws[l_off:l_off + 16 * n].view(np.int32).reshape(n, 4)
+        cu = b["cu_seqlens"]
+        want = {(int(cu[i]), x, min(x, 40) if used else x, r) for i, x in enumerate(lengths) for r in range(0, x, 128)}
+        assert n == len(want) and {tuple(x) for x in items.tolist()} == want
+        assert (np.diff(np.minimum((items[:, 2] + 7) // 8, 127)) <= 0).all()
+    d.o.fill_(float("nan"))
+    d.lse.fill_(float("nan"))
+    d.fwd(reuse_schedule=True)
+    assert torch.equal(d.o.view(torch.int16), o.view(torch.int16))
+    assert torch.equal(d.lse.view(torch.int32), lse.view(torch.int32))
+    d.bwd(reuse_schedule=True)
+    torch.cuda.synchronize()
+    if b["total_tokens"] and not used:
+        x = oracle_inputs(b)
+        o_ref, _ = oracle.fwd(x["q"], x["k"], x["v"], b["cu_seqlens"], b["scale"])
+        assert np.abs(to_f64(d.o) - o_ref).max() <= O_TOL + ulp_half(np.abs(o_ref), "bf16").max()
+        for got, want in zip((d.dq, d.dk, d.dv), oracle.bwd(x["q"], x["k"], x["v"], x["do"], b["cu_seqlens"], b["scale"])):
+            rel, fro = gradient_errors(to_f64(got), want, b["cu_seqlens"])
+            assert rel <= G_TOL and fro <= G_TOL
+
+
 def test_padded_layout_with_key_mask_matches_packed():
     b = wl.make_batch([5, 130, 64, 1, 77], 2, "f16", seed=11)
     db = run(b, True)
