@@ -339,6 +339,7 @@ __global__ __launch_bounds__(kLnColsThreads) void ln_bwd_cols_kernel(const float
                                                                      int n, float* __restrict__ dgamma,
                                                                      float* __restrict__ dbeta) {
   constexpr int kWaves = kLnColsThreads / 64;
+  constexpr int kAhead = 16;  // loads in flight: all partial rows of 256 workgroups in one round trip
   __shared__ float part[kWaves][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int which = blockIdx.y;
@@ -348,6 +349,13 @@ __global__ __launch_bounds__(kLnColsThreads) void ln_bwd_cols_kernel(const float
     const float* p = partial + (int64_t)which * n + c;
     const int64_t step = 2 * (int64_t)n;
     int b = wave;
+    for (; b + (kAhead - 1) * kWaves < n_partial; b += kAhead * kWaves) {
+      float x[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; u++) x[u] = p[(int64_t)(b + u * kWaves) * step];
+#pragma unroll
+      for (int u = 0; u < kAhead; u++) s[u & 3] += x[u];
+    }
     for (; b + 3 * kWaves < n_partial; b += 4 * kWaves) {
 #pragma unroll
       for (int u = 0; u < 4; u++) s[u] += p[(int64_t)(b + u * kWaves) * step];
