@@ -77,6 +77,9 @@ extern "C" int fmha_embedding_sort(const int32_t* indices, const int32_t* n_rows
   a.vocab = vocab;
   a.padding_idx = padding_idx;
   a.tiles = s.tiles;
+  const bool sum_in_place = s.tiles <= fmha::kSortSumInPlace;
+  a.tile_stride = sum_in_place ? fmha::kSortDigits : 1;
+  a.digit_stride = sum_in_place ? 1 : s.tiles;
   a.bits = (key_size + passes - 1) / passes;
   if (rows <= fmha::kSortSmall) {
     a.out = buffers[0];
@@ -90,7 +93,7 @@ extern "C" int fmha_embedding_sort(const int32_t* indices, const int32_t* n_rows
       a.out = buffers[(passes - 1 - p) & 1];  // the last pass writes the result
       a.shift = p * a.bits;
       fmha::sort_count_kernel<<<(unsigned)s.tiles, fmha::kSortThreads, 0, st>>>(a);
-      if (s.tiles <= fmha::kSortSumInPlace) {
+      if (sum_in_place) {
         fmha::sort_place_kernel<true><<<(unsigned)s.tiles, fmha::kSortThreads, 0, st>>>(a);
       } else {
         fmha::sort_tiles_kernel<<<fmha::kSortDigits, fmha::kSortThreads, 0, st>>>(a);
