@@ -145,9 +145,12 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _tok_stride(t: torch.Tensor) -> int:
-    assert t.dim() == 3 and t.stride(2) == 1 and t.stride(1) == t.shape[2], \
+    # one call each for all strides and sizes: asking one by one is 0.7 us more per tensor, and a
+    # small forward call (8 us on the GPU) asks for four of them
+    stride, shape = t.stride(), t.shape
+    assert len(shape) == 3 and stride[2] == 1 and stride[1] == shape[2], \
         "tensors are [T, H, 64] with heads contiguous inside a token"
-    return t.stride(0) if t.shape[0] > 1 else t.shape[1] * t.shape[2]
+    return stride[0] if shape[0] > 1 else shape[1] * shape[2]
 
 
 def fmha_varlen_workspace_size(batch: int, total_tokens: int, heads: int, need_bwd: bool) -> int:
