@@ -95,6 +95,15 @@ def test_layernorm_with_dropout(rows, hidden, p, dtype):
     Run(rows, hidden, dtype, seed=rows + hidden, p=p, dseed=0x1234567811223344 + rows).check()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("hidden", [496, 512, 528, 1008, 1536, 1552])
+def test_layernorm_at_the_edges_of_a_lanes_two_pieces(hidden, dtype):
+    """A lane has columns in two pieces, 512 apart: rows that end inside the first, at its end,
+    just after it, inside the second, and the same in a lane's second pair of pieces; the lanes of
+    a pair trade the mask bytes of both pieces."""
+    Run(11, hidden, dtype, seed=hidden, p=0.2, dseed=hidden * 1000003).check()
+
+
 def test_layernorm_many_rows_bert_large_shape():
     """Workload 3's token count x BERT-large hidden size: every persistent wavefront takes
     several rows and the column sums span hundreds of workgroups' partial results."""
