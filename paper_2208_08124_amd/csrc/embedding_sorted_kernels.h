@@ -192,11 +192,13 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
 }
 
 // One workgroup per chunk in which a run begins that goes on into later chunks: its partial
-// sums are added in chunk order and the row is written.  Where the run ends is found first (a
-// binary search in the sorted indices by one thread), so that the partial sums - up to a few
-// hundred for the most frequent index of a large batch, and its one workgroup is what the
-// kernel waits for - can then be fetched kEmbCombineAhead at a time and added in order
-// (527340 Zipf-distributed rows of 768: 60 us with four at a time, 22 with sixteen).
+// sums are added in chunk order and the row is written.  Where the run ends is found first (the
+// first later chunk that it does not cover whole, all threads looking at a chunk each: a binary
+// search in the sorted indices was a chain of 15 - 19 memory round trips), so that the partial
+// sums - up to a few hundred for the most frequent index of a large batch, and its one
+// workgroup is what the kernel waits for - can then be fetched kEmbCombineAhead at a time and
+// added in order (527340 Zipf-distributed rows of 768: 60 us with four at a time, 22 with
+// sixteen, 18 without the search; 65536 rows 87 -> 81 us in all).
 constexpr int kEmbCombineAhead = 16;
 template <bool BF16>
 __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbSortedArgs a, const int chunk) {
@@ -204,18 +206,17 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbS
   const int c = blockIdx.x;
   const int key = a.info[c].tail_key;
   if (key < 0) return;
-  if (threadIdx.x == 0) {
-    int lo = (c + 1) * chunk, hi = a.rows;  // first position after the run: keys[lo - 1] == key < keys[hi] (or hi == rows)
-    while (lo < hi) {
-      const int mid = lo + ((hi - lo) >> 1);
-      if (a.sorted[mid].x <= (uint32_t)key)
-        lo = mid + 1;
-      else
-        hi = mid;
-    }
-    s_last = (lo - 1) / chunk;  // the chunk the run ends in
-  }
+  const int chunks = (a.rows - 1) / chunk + 1;
+  if (threadIdx.x == 0) s_last = chunks;
   __syncthreads();
+  for (int d0 = c + 1;; d0 += kEmbSortThreads) {
+    const int d = min(d0 + (int)threadIdx.x, chunks - 1);  // (a run ends in the last chunk at the latest)
+    if (!a.info[d].head_whole) atomicMin(&s_last, d);
+    __syncthreads();
+    const bool found = s_last < chunks;
+    __syncthreads();
+    if (found) break;
+  }
   const int d_last = s_last;
   const int hidden = 2 * a.pairs;
   uint16_t* dw = reinterpret_cast<uint16_t*>(a.dw);
