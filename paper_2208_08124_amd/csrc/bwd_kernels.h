@@ -9,9 +9,8 @@
 //       dV^T += dO^T P,  dK^T += Q^T dS.
 //
 // With dropout (DROP) the mask M is regenerated from the seed (dropout.h):
-// dP = (dO V^T) o M / (1-p) in both passes and dV^T += dO^T (P o M) / (1-p);
-// D = rowsum(dO o O) as before.  Pass 2 has the factor in its probabilities: pass 1
-// stores LSE and D for it with the factor worked in.
+// dP = (dO V^T) o M / (1-p) in both passes and dV^T += dO^T (P o M) with the
+// factor 1/(1-p) applied to the finished rows; D = rowsum(dO o O) as before.
 //
 // Both orientations are chosen so that the MFMA result tile of the first two
 // products has, in every lane, the reduction index of the following product
@@ -67,13 +66,11 @@ __device__ __forceinline__ void dq_block(f32x16 (&dq)[2], const uint16_t* sK, co
     for (int t = 0; t < 4; t++) {
       s = Op<T>::mfma(ka[t], qb[t], t == 0 ? zero : s);
       if (DROP) {
-        hold(s);
         keep.round();
         __builtin_amdgcn_sched_barrier(0);
       }
       dp = Op<T>::mfma(va[t], gb[t], t == 0 ? zero : dp);
       if (DROP) {
-        hold(dp);
         keep.round();
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -266,10 +263,8 @@ __global__ __launch_bounds__(kThreads, DROP ? 2 : 3) void bwd_dq_kernel(const Bw
       const int row = ti.row0 + 32 * wave + (le & 31);
       if (row < len && le < 32) {
         const int64_t si = (int64_t)head * a.pb.total_tokens + r0 + row;
-        // With dropout pass 2 wants the probabilities times rp = 1/(1-p): what is kept is then
-        // P o M as it stands, and dS = (P o M) o dP - (rp P) o (D / rp) one multiply-add more.
-        a.dsum[si] = DROP ? dsum * (1.f / a.drop.rp) : dsum;
-        a.lse2[si] = DROP ? lse2 - __builtin_amdgcn_logf(a.drop.rp) : lse2;
+        a.dsum[si] = dsum;
+        a.lse2[si] = lse2;
       }
     }
     // dQ leaves as whole rows, turned around in the wavefront's private rows of
@@ -318,13 +313,11 @@ __device__ __forceinline__ void dkv_block(f32x16 (&dk)[2], f32x16 (&dv)[2], cons
   for (int t = 0; t < 4; t++) {
     s = Op<T>::mfma(qa[t], kb4[t], t == 0 ? zero : s);
     if (DROP) {
-      hold(s);
       keep.round();
       __builtin_amdgcn_sched_barrier(0);
     }
     dp = Op<T>::mfma(ga[t], vb4[t], t == 0 ? zero : dp);
     if (DROP) {
-      hold(dp);
       keep.round();
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -357,10 +350,9 @@ __device__ __forceinline__ void dkv_block(f32x16 (&dk)[2], f32x16 (&dv)[2], cons
     for (int e = 0; e < 4; e++) {
       const float pe = fast_exp2(__builtin_fmaf(s[4 * j + e], c2, -lv[e]));
       if (DROP) {
-        // pe carries the factor 1/(1-p) and dvv its inverse (pass 1 left both that way)
-        const float pm = kept(kb8, 4 * j + e, drop.thr) ? pe : 0.f;
-        p[4 * j + e] = pm;
-        ds[4 * j + e] = __builtin_fmaf(pm, dp[4 * j + e], -(pe * dvv[e]));
+        const bool on = kept(kb8, 4 * j + e, drop.thr);
+        p[4 * j + e] = on ? pe : 0.f;
+        ds[4 * j + e] = pe * (on ? __builtin_fmaf(dp[4 * j + e], drop.rp, -dvv[e]) : -dvv[e]);
       } else {
         p[4 * j + e] = pe;
         ds[4 * j + e] = pe * (dp[4 * j + e] - dvv[e]);
@@ -521,7 +513,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkv_kernel(const BwdArgs a) {
       const int n_rows = len - (ti.row0 + 32 * wave);
       store_rows<T>(dk, a.pb.scale, ring[kBwdStages - 1].q, wave, a.dk, tok * a.dk_stride + head * kHeadDim,
                     a.dk_stride, n_rows);
-      store_rows<T>(dv, 1.f, ring[kBwdStages - 2].q, wave, a.dv, tok * a.dv_stride + head * kHeadDim,
+      store_rows<T>(dv, DROP ? a.drop.rp : 1.f, ring[kBwdStages - 2].q, wave, a.dv, tok * a.dv_stride + head * kHeadDim,
                     a.dv_stride, n_rows);
     }
     item = item1;

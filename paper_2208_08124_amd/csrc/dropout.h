@@ -72,13 +72,10 @@ static __device__ __forceinline__ uint32_t quad_rotate(uint32_t x) {
 // finish() returns four words; byte e of word j belongs to register 4j + e.
 // All 64 lanes must be active.
 //
-// The kernels write one round (two multiplications and two v_bitop3 in a serial chain) after
-// each MFMA of the tile's first products and hold both in place; left to itself the compiler
-// puts all rounds ahead of the first MFMA.  Beside another wavefront on the SIMD that is worth
-// little: what counts is the number of vector instructions.  On a BERT-large micro-batch, p = 0.1,
-// forward and backward: 290 us with two v_xor per key addition, 276 with one v_bitop3 and the
-// factor 1/(1-p) in a multiply-add, 274 with the rounds held in place, 270 with that factor in
-// the dK/dV pass's probabilities.
+// The rounds (two multiplications of 16 cycles and two v_bitop3 each, in one serial chain) take
+// about as long as the tile's first products (8 MFMAs of 32 cycles).  The kernels write one round
+// after each MFMA, fenced: left to itself the compiler puts all rounds ahead of the first MFMA,
+// and the wavefront's matrix and vector work then follow each other instead of overlapping.
 template <bool TRANSPOSED>
 struct KeepGen {
   Philox p;
@@ -91,10 +88,7 @@ struct KeepGen {
     p = TRANSPOSED ? Philox{(uint32_t)col4, (uint32_t)blk, (uint32_t)r0, (uint32_t)head, k0, k1}
                    : Philox{(uint32_t)blk, (uint32_t)col4, (uint32_t)r0, (uint32_t)head, k0, k1};
   }
-  __device__ __forceinline__ void round() {
-    p.round();
-    asm volatile("" : "+v"(p.c0));  // (the fence alone does not hold a round in its place)
-  }
+  __device__ __forceinline__ void round() { p.round(); }
   __device__ __forceinline__ void finish(uint32_t (&out)[4], int ln) const {
     const int b = ln & 3;
     const int c = (ln >> 3) & 3;  // (column >> 3) & 3: tile bases are multiples of 32
@@ -126,10 +120,6 @@ struct KeepGen {
     for (int j = 0; j < 4; j++) out[j] = (b & 2) ? r1[(j + 2) & 3] : r1[j];
   }
 };
-
-// Keeps the MFMA that forms x where it is written, among the rounds (no instruction; the fences
-// alone order neither, because neither touches memory).
-static __device__ __forceinline__ void hold(f32x16& x) { asm volatile("" : "+v"(x)); }
 
 // The same in one go.
 template <bool TRANSPOSED>

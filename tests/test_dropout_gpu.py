@@ -252,3 +252,48 @@ def test_dropout_large_batch_bf16_sampled():
         for name, got, want in zip(("dq", "dk", "dv"), (db.dq, db.dk, db.dv), g_ref):
             rel = np.abs(to_f64(got[sl]) - want).max() / max(np.abs(want).max(), G_FLOOR)
             assert rel <= G_TOL, f"sequence {i} {name}: {rel:.3e}"
+
+
+def test_dkv_pass_takes_the_statistics_of_any_dq_pass():
+    """The statistics the dQ pass leaves in the workspace (D and the log-sum-exp) are functions
+    of o, d_o and lse alone, so a dK/dV pass run by itself gives the same bits after a dQ pass
+    with its own dropout, with another one, and without dropout."""
+    b = wl.make_batch([130, 1, 77], 2, "f16", seed=616)
+    db = DeviceBatch(b, True)
+    drop = (0.25, 1234)
+    db.fwd(dropout=drop)
+    db.bwd(reuse_schedule=True, dropout=drop)
+    dk, dv = db.dk.clone(), db.dv.clone()
+    for other in (drop, (0.5, 99), None):
+        db.dk.fill_(float("nan"))
+        db.dv.fill_(float("nan"))
+        db.bwd(reuse_schedule=True, only="dq", dropout=other)
+        db.bwd(reuse_schedule=True, only="dkv", dropout=drop)
+        torch.cuda.synchronize()
+        assert torch.equal(db.dk, dk) and torch.equal(db.dv, dv), other
+
+
+def test_infinite_product_at_a_dropped_score():
+    """dO V^T overflows fp32 at one (query, key) pair that the mask drops: its dS is -P D like that
+    of every dropped score, in both passes, and no gradient sees the infinity."""
+    n, p, seed = 70, 0.5, 4711
+    b = wl.make_batch([n], 1, "bf16", seed=21)
+    keep = dm.keep_masks(b["cu_seqlens"], 1, p, seed)[0][0]
+    q, k = next((q, k) for q in range(33, n) for k in range(5, n) if not keep[q, k])
+    for name in ("v", "do"):
+        b[name][:, 0, 0] = 0
+    huge = wl.to_bits(np.array([2e20], np.float32), "bf16")[0]
+    b["v"][k, 0, 0] = huge
+    b["do"][q, 0, 0] = huge
+    db = DeviceBatch(b, True)
+    db.fwd(dropout=(p, seed))
+    db.bwd(reuse_schedule=True, dropout=(p, seed))
+    torch.cuda.synchronize()
+    x = oracle_inputs(b)
+    dq, dk, dv = oracle.bwd_dropout(x["q"], x["k"], x["v"], x["do"], b["cu_seqlens"], b["scale"], [keep[None]],
+                                    dm.keep_scale(p), None)
+    for name, got, want in (("dq", db.dq, dq), ("dk", db.dk, dk), ("dv", db.dv[:, :, 1:], dv[:, :, 1:])):
+        g = to_f64(got)
+        assert np.isfinite(g).all(), name
+        rel = np.abs(g - want).max() / max(np.abs(want).max(), G_FLOOR)
+        assert rel <= G_TOL, f"{name}: {rel:.3e}"
