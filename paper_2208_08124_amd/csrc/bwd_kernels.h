@@ -59,27 +59,13 @@ __device__ __forceinline__ void dq_block(f32x16 (&dq)[2], const uint16_t* sK, co
     }
     __builtin_amdgcn_sched_barrier(0);
     f32x16 s, dp;
-    uint32_t kb8[4];  // mask bytes: independent of the products, made beside them
-    KeepGen<false> keep;
-    if (DROP) keep.begin(q4, ((key_base + 32 * kb) >> 2) + g, ln, r0, head, drop);
 #pragma unroll
     for (int t = 0; t < 4; t++) {
       s = Op<T>::mfma(ka[t], qb[t], t == 0 ? zero : s);
-      if (DROP) {
-        keep.round();
-        __builtin_amdgcn_sched_barrier(0);
-      }
       dp = Op<T>::mfma(va[t], gb[t], t == 0 ? zero : dp);
-      if (DROP) {
-        keep.round();
-        __builtin_amdgcn_sched_barrier(0);
-      }
     }
-    if (DROP) {
-      keep.round();
-      keep.round();
-      keep.finish(kb8, ln);
-    }
+    uint32_t kb8[4];  // mask bytes: independent of the products just issued
+    if (DROP) keep_bytes<false>(kb8, q4, ((key_base + 32 * kb) >> 2) + g, ln, r0, head, drop);
     __builtin_amdgcn_sched_barrier(0);
     u32x4 kT[2][2];
 #pragma unroll
@@ -93,9 +79,8 @@ __device__ __forceinline__ void dq_block(f32x16 (&dq)[2], const uint16_t* sK, co
     for (int r = 0; r < 16; r++) {
       float p = fast_exp2(__builtin_fmaf(s[r], c2, -lse2));
       if (RAGGED && key0 + 8 * (r >> 2) + (r & 3) >= nk) p = 0.f;
-      // (the factor and the subtraction in one multiply-add, the mask behind it)
-      const float dpr = DROP ? (kept(kb8, r, drop.thr) ? __builtin_fmaf(dp[r], drop.rp, -dsum) : -dsum) : dp[r] - dsum;
-      ds[r] = p * dpr;
+      const float dpr = DROP ? (kept(kb8, r, drop.thr) ? dp[r] * drop.rp : 0.f) : dp[r];
+      ds[r] = p * (dpr - dsum);
     }
     u32x4 dsb[2];
 #pragma unroll
@@ -306,27 +291,13 @@ __device__ __forceinline__ void dkv_block(f32x16 (&dk)[2], f32x16 (&dv)[2], cons
   __builtin_amdgcn_sched_barrier(0);
   // S = Q K^T, dP = dO V^T : rows = queries (32), column = key ln
   f32x16 s, dp;
-  uint32_t kb8[4];  // mask bytes: independent of the products, made beside them
-  KeepGen<true> keep;
-  if (DROP) keep.begin(k4, ((q_base + 32 * qb) >> 2) + g, ln, r0, head, drop);
 #pragma unroll
   for (int t = 0; t < 4; t++) {
     s = Op<T>::mfma(qa[t], kb4[t], t == 0 ? zero : s);
-    if (DROP) {
-      keep.round();
-      __builtin_amdgcn_sched_barrier(0);
-    }
     dp = Op<T>::mfma(ga[t], vb4[t], t == 0 ? zero : dp);
-    if (DROP) {
-      keep.round();
-      __builtin_amdgcn_sched_barrier(0);
-    }
   }
-  if (DROP) {
-    keep.round();
-    keep.round();
-    keep.finish(kb8, ln);
-  }
+  uint32_t kb8[4];  // mask bytes: independent of the products just issued
+  if (DROP) keep_bytes<true>(kb8, k4, ((q_base + 32 * qb) >> 2) + g, ln, r0, head, drop);
   __builtin_amdgcn_sched_barrier(0);
   // rows 32qb + 8j + 4g + {0..3}: their statistics sit side by side
   float4 l4[4], d4[4];
@@ -352,7 +323,7 @@ __device__ __forceinline__ void dkv_block(f32x16 (&dk)[2], f32x16 (&dv)[2], cons
       if (DROP) {
         const bool on = kept(kb8, 4 * j + e, drop.thr);
         p[4 * j + e] = on ? pe : 0.f;
-        ds[4 * j + e] = pe * (on ? __builtin_fmaf(dp[4 * j + e], drop.rp, -dvv[e]) : -dvv[e]);
+        ds[4 * j + e] = pe * ((on ? dp[4 * j + e] * drop.rp : 0.f) - dvv[e]);
       } else {
         p[4 * j + e] = pe;
         ds[4 * j + e] = pe * (dp[4 * j + e] - dvv[e]);

@@ -63,7 +63,6 @@ __device__ __forceinline__ void fwd_block(FwdAcc& acc, const uint16_t* sK, const
   // S^T = K Q^T : rows = keys (two blocks of 32), column = query ln
   f32x16 s[2];
   const bool one_half = RAGGED && key_base + 32 >= nk;  // uniform: no key in the second 32
-  uint32_t kb8[2][4];  // mask bytes: independent of the scores, made beside their products
   {
     u32x4 ka[4][2];
 #pragma unroll
@@ -72,44 +71,22 @@ __device__ __forceinline__ void fwd_block(FwdAcc& acc, const uint16_t* sK, const
       for (int kb = 0; kb < 2; kb++)
         if (kb == 0 || !one_half) ka[t][kb] = rr.read(sK, kb, t);
     __builtin_amdgcn_sched_barrier(0);
-    KeepGen<false> keep[2];
-    if (DROP) {
-      keep[0].begin(q4, (key_base >> 2) + g, ln, r0, head, drop);
-      if (!one_half) keep[1].begin(q4, ((key_base + 32) >> 2) + g, ln, r0, head, drop);
-    }
     if (one_half) {
 #pragma unroll
-      for (int t = 0; t < 4; t++) {
-        s[0] = Op<T>::mfma(ka[t][0], qb[t], t == 0 ? zero : s[0]);
-        if (DROP) {
-          keep[0].round();
-          keep[0].round();
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
+      for (int t = 0; t < 4; t++) s[0] = Op<T>::mfma(ka[t][0], qb[t], t == 0 ? zero : s[0]);
     } else {
 #pragma unroll
       for (int t = 0; t < 4; t++)
 #pragma unroll
-        for (int kb = 0; kb < 2; kb++) {
-          s[kb] = Op<T>::mfma(ka[t][kb], qb[t], t == 0 ? zero : s[kb]);
-          if (DROP) {
-            keep[0].round();
-            keep[1].round();
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
+        for (int kb = 0; kb < 2; kb++) s[kb] = Op<T>::mfma(ka[t][kb], qb[t], t == 0 ? zero : s[kb]);
     }
-    if (DROP) {
-      keep[0].round();
-      keep[0].round();
-      keep[0].finish(kb8[0], ln);
-      if (!one_half) {
-        keep[1].round();
-        keep[1].round();
-        keep[1].finish(kb8[1], ln);
-      }
-    }
+  }
+  // the mask bytes do not depend on the scores: their arithmetic fills the time the
+  // matrix cores need for the products just issued
+  uint32_t kb8[2][4];
+  if (DROP) {
+    keep_bytes<false>(kb8[0], q4, (key_base >> 2) + g, ln, r0, head, drop);
+    if (!one_half) keep_bytes<false>(kb8[1], q4, ((key_base + 32) >> 2) + g, ln, r0, head, drop);
   }
   __builtin_amdgcn_sched_barrier(0);
   const int key0 = key_base + 4 * g;      // key of s[0][0]

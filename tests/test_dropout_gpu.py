@@ -297,3 +297,29 @@ def test_infinite_product_at_a_dropped_score():
         assert np.isfinite(g).all(), name
         rel = np.abs(g - want).max() / max(np.abs(want).max(), G_FLOOR)
         assert rel <= G_TOL, f"{name}: {rel:.3e}"
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_scaled_product_is_rounded_before_d_is_subtracted(dtype):
+    """dP = round(dO V^T / (1-p)) and then dS = P (dP - D), in both passes.  Single-token sequences
+    with P = 1, dO V^T = 1.5, 1/(1-p) = 4/3 in fp32 (1.33333337), D = 2: the product rounds to 2
+    and a kept element's gradients are exactly zero; in one multiply-add 6e-8 would be left.  A
+    dropped element has dS = -2."""
+    n, h, p, seed = 40, 2, 0.25, 12
+    b = wl.make_batch([1] * n, h, dtype, seed=1)
+    one = lambda x: wl.to_bits(np.array([x], np.float32), dtype)[0]
+    for name, column, value in (("q", 1, 64.0), ("k", 0, 64.0), ("v", 0, 1.5), ("do", 0, 1.0)):
+        b[name][:] = 0
+        b[name][:, :, column] = one(value)
+    b["scale"] = 0.5
+    db = DeviceBatch(b, True)
+    db.o.zero_()
+    db.o[:, :, 0] = 2.0
+    db.lse.zero_()                    # the one score is q k = 0, so P = 1
+    db.bwd(dropout=(p, seed))
+    torch.cuda.synchronize()
+    keep = np.stack([dm.keep_masks(b["cu_seqlens"], h, p, seed)[i][:, 0, 0] for i in range(n)])  # [n, h]
+    assert 0 < keep.sum() < keep.size
+    dq, dk = to_f64(db.dq), to_f64(db.dk)
+    assert np.array_equal(dq[:, :, 0], np.where(keep, 0.0, -64.0)) and (dq[:, :, 1:] == 0).all()
+    assert np.array_equal(dk[:, :, 1], np.where(keep, 0.0, -64.0)) and (dk[:, :, 0] == 0).all() and (dk[:, :, 2:] == 0).all()
