@@ -51,7 +51,7 @@ struct Cvt<__bf16> {
   static __device__ __forceinline__ float hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
 };
 
-// A lane's columns in trip i: two pieces of eight, `half` columns apart; a row ends at a
+// A lane's columns in trip i: two pieces of eight, 512 columns apart; a row ends at a
 // multiple of 16, so both lanes of a pair (2m, 2m + 1) have a piece or neither has it.
 struct LnCols {
   int c[2];
@@ -274,7 +274,9 @@ __global__ __launch_bounds__(kLnBwdThreads / CPL) void ln_bwd_rows_kernel(const 
 #pragma unroll
     for (int i = 0; i < CPL; i++) {
       const LnCols cols(lane, i, n);
-      if (cols.on[0]) {  // (a piece past the end has dy = 0 and adds nothing)
+      if (cols.on[0]) {
+        // (a piece past the end has dy = z = 0; its xh has to be zero too: -mean rstd may overflow)
+        const float mp[2] = {mean, cols.on[1] ? mean : 0.f}, rp[2] = {rs, cols.on[1] ? rs : 0.f};
         float dyf[16], zf[16], gf[16];
         const Raw16 dyr = load16_raw(dy + base, cols), zr = load16_raw(z + base, cols);
         load16f(gamma, cols, gf);
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(kLnBwdThreads / CPL) void ln_bwd_rows_kernel(const 
         unpack16<T>(zr, zf);
 #pragma unroll
         for (int k = 0; k < 16; k++) {
-          xh[i][k] = (zf[k] - mean) * rs;
+          xh[i][k] = (zf[k] - mp[k >> 3]) * rp[k >> 3];
           g[i][k] = dyf[k] * gf[k];
           s1 += g[i][k];
           s2 = __builtin_fmaf(g[i][k], xh[i][k], s2);

@@ -104,6 +104,36 @@ def test_layernorm_at_the_edges_of_a_lanes_two_pieces(hidden, dtype):
     Run(11, hidden, dtype, seed=hidden, p=0.2, dseed=hidden * 1000003).check()
 
 
+@pytest.mark.parametrize("hidden", [16, 256, 512, 1024, 2048])
+def test_layernorm_rows_of_one_large_value(hidden):
+    """Rows that hold one value of 1e33, eps = 1e-12: mean = that value and var = 0 exactly (powers of
+    two columns), so xh = 0, rstd = 1e6 and every result is finite.  The columns a lane has no
+    piece of must not enter: (0 - mean) rstd overflows."""
+    rows, c = 5, 1e33
+    g = torch.Generator(device="cuda").manual_seed(hidden)
+    x = torch.zeros((rows, hidden), dtype=torch.bfloat16, device="cuda")
+    r = torch.full_like(x, c)
+    dy = torch.randn((rows, hidden), generator=g, device="cuda").to(torch.bfloat16)
+    gamma, beta = (1 + 0.2 * torch.randn(hidden, generator=g, device="cuda") for _ in range(2))
+    y, z, dx, dr = (torch.full_like(x, float("nan")) for _ in range(4))
+    mu, rstd = (torch.full((rows,), float("nan"), device="cuda") for _ in range(2))
+    dgamma, dbeta = (torch.full((hidden,), float("nan"), device="cuda") for _ in range(2))
+    ws = torch.empty(fmha.fmha_dropout_add_ln_bwd_workspace_size(rows, hidden), dtype=torch.uint8, device="cuda")
+    fmha.fmha_dropout_add_ln_fwd(x, r, gamma, beta, 1e-12, y, z, mu, rstd)
+    fmha.fmha_dropout_add_ln_bwd(dy, z, mu, rstd, gamma, 1e-12, dx, dr, dgamma, dbeta, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(z, r) and torch.equal(mu, r[:, 0].float())
+    want_y = beta.double().cpu().numpy()
+    assert (np.abs(to_f64(y) - want_y) <= 2e-3 + 2 * ulp_half(want_y, "bf16")).all()
+    gd = to_f64(dy) * gamma.double().cpu().numpy()
+    want = to_f64(rstd)[:, None] * (gd - gd.mean(axis=1, keepdims=True))
+    for name, got in (("dx", dx), ("dr", dr)):
+        assert np.abs(to_f64(got) - want).max() <= 1e-2 * np.abs(want).max(), name
+    assert (dgamma == 0).all()
+    want = to_f64(dy).sum(axis=0)
+    assert np.abs(to_f64(dbeta) - want).max() <= 1e-2 * np.abs(want).max()
+
+
 def test_layernorm_many_rows_bert_large_shape():
     """Workload 3's token count x BERT-large hidden size: every persistent wavefront takes
     several rows and the column sums span hundreds of workgroups' partial results."""
