@@ -88,8 +88,12 @@ int fmha_unpad_indices(const int32_t* input_mask, int32_t batch, int32_t seqlen,
     fmha::prefix_sum_kernel<<<1, fmha::kScanThreads, 0, st>>>(cu_seqlens, 0);
     return launched("prefix sum");
   }
+  // One launch reads the mask in workgroups that follow no order, three read an entry for the last
+  // time in the thread that then writes its inverse: `inverse` may be the mask itself only there.
   const int64_t entries = (int64_t)batch * seqlen;
-  if (entries <= kMaskAllEntries && entries * batch <= kMaskAllReads) {
+  const uintptr_t m0 = reinterpret_cast<uintptr_t>(input_mask), i0 = reinterpret_cast<uintptr_t>(inverse);
+  const bool shared = inverse && m0 < i0 + 4 * (uintptr_t)entries && i0 < m0 + 4 * (uintptr_t)entries;
+  if (!shared && entries <= kMaskAllEntries && entries * batch <= kMaskAllReads) {
     fmha::mask_all_kernel<<<(unsigned)batch, fmha::kMaskAllThreads, 0, st>>>(input_mask, batch, seqlen, cu_seqlens, nonzero_indices, inverse);
     return launched("mask");
   }

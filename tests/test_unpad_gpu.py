@@ -61,6 +61,22 @@ def test_device_indices_bit_exact(name, m):
     assert np.array_equal(inv.cpu().numpy(), rinv)
 
 
+@pytest.mark.parametrize("shape", [(56, 512), (3, 2500), (300, 40), (2500, 512)])
+def test_inverse_may_take_the_place_of_the_mask(shape):
+    """fmha_unpad_indices with inverse == input_mask: an entry is read for the last time where its
+    inverse is written, whatever the size."""
+    m = (RNG.random(shape) < 0.7).astype(np.int32)
+    ridx, rinv, rcu = unpad.unpad_indices(m)
+    dm = torch.from_numpy(m).cuda()
+    idx = torch.full((m.size,), -7, dtype=torch.int32, device="cuda")
+    cu = torch.full((shape[0] + 1,), -7, dtype=torch.int32, device="cuda")
+    fmha.fmha_unpad_indices(dm, idx, dm, cu)
+    torch.cuda.synchronize()
+    assert np.array_equal(cu.cpu().numpy(), rcu)
+    assert np.array_equal(idx.cpu().numpy()[:len(ridx)], ridx)
+    assert np.array_equal(dm.cpu().numpy().reshape(-1), rinv)
+
+
 @pytest.mark.parametrize("row_elems", [8, 64, 1024, 1032])
 def test_gather_scatter_bit_exact(row_elems):
     lengths = [5, 0, 128, 77, 1]
