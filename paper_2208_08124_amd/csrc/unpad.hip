@@ -31,11 +31,14 @@ int check_rows(const void* src, const void* dst, const int32_t* map, const int32
   return FMHA_OK;
 }
 
-// Where unpad_indices takes one launch instead of three (mask_all_kernel): a bound on what the
-// last row's workgroup reads, and one on what all of them read together (half of it).  us with
-// three launches / with one: 56 x 512 9.0 / 3.9, 256 x 256 7.8 / 5.3, 128 x 1024 11.9 / 7.1 (both
-// bounds reached); beyond, 512 x 128 7.1 / 6.7, 1024 x 32 6.9 / 8.1, 1024 x 128 7.2 / 14.8.
+// Where unpad_indices takes one launch instead of three (mask_all_kernel): bounds on what the last
+// row's workgroup reads, on what all of them read together (half of it), and on their number (512
+// of 1024 threads run at once).  us with three launches / with one: 56 x 512 8.9 / 3.8, 256 x 256
+// 7.6 / 5.2, 128 x 1024 11.8 / 7.3 (both first bounds reached), 1024 x 8 7.1 / 6.3, 1024 x 16 7.0 /
+// 7.0; beyond, 512 x 128 7.1 / 6.7, 1024 x 32 6.9 / 8.1, 1024 x 128 7.2 / 14.8, 2048 x 3 7.9 / 10.0,
+// 4096 x 1 9.3 / 18.
 constexpr int64_t kMaskAllEntries = 131072, kMaskAllReads = (int64_t)1 << 24;
+constexpr int32_t kMaskAllRows = 1024;
 
 unsigned copy_grid(int64_t rows, int64_t chunks) {
   const int64_t want = (rows * chunks + 1023) / 1024;  // four pieces per thread and trip
@@ -93,7 +96,7 @@ int fmha_unpad_indices(const int32_t* input_mask, int32_t batch, int32_t seqlen,
   const int64_t entries = (int64_t)batch * seqlen;
   const uintptr_t m0 = reinterpret_cast<uintptr_t>(input_mask), i0 = reinterpret_cast<uintptr_t>(inverse);
   const bool shared = inverse && m0 < i0 + 4 * (uintptr_t)entries && i0 < m0 + 4 * (uintptr_t)entries;
-  if (!shared && entries <= kMaskAllEntries && entries * batch <= kMaskAllReads) {
+  if (!shared && batch <= kMaskAllRows && entries <= kMaskAllEntries && entries * batch <= kMaskAllReads) {
     fmha::mask_all_kernel<<<(unsigned)batch, fmha::kMaskAllThreads, 0, st>>>(input_mask, batch, seqlen, cu_seqlens, nonzero_indices, inverse);
     return launched("mask");
   }

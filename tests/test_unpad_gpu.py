@@ -39,12 +39,14 @@ def masks():
     yield "empty_rows", np.zeros((5, 70), dtype=np.int32)
     yield "workload3", prefix_mask(wl.make_workload(3)["lengths"], 512)
     yield "many_rows", prefix_mask(RNG.integers(0, 513, size=2500), 512)   # more rows than scan threads
-    # the edges of the one-launch form: 131072 entries, batch^2 * columns = 2^24, rows longer than
+    # the edges of the one-launch form: 131072 entries, batch^2 * columns = 2^24, 1024 rows, rows longer than
     # a workgroup, a mask that is not 16-byte aligned in its later rows
     yield "one_launch_most_entries", (RNG.random((128, 1024)) < 0.7).astype(np.int32)
     yield "three_launches_by_entries", (RNG.random((127, 1033)) < 0.7).astype(np.int32)
     yield "one_launch_most_reads", (RNG.random((256, 256)) < 0.7).astype(np.int32)
     yield "three_launches_by_reads", (RNG.random((257, 255)) < 0.7).astype(np.int32)
+    yield "one_launch_most_rows", (RNG.random((1024, 9)) < 0.7).astype(np.int32)
+    yield "three_launches_by_rows", (RNG.random((1025, 9)) < 0.7).astype(np.int32)
     yield "long_rows", (RNG.random((3, 2500)) < 0.7).astype(np.int32)
     yield "no_columns", np.zeros((4, 0), dtype=np.int32)
     yield "no_rows", np.zeros((0, 16), dtype=np.int32)
