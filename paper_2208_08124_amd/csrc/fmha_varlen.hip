@@ -366,14 +366,15 @@ int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   hipStream_t st = static_cast<hipStream_t>(stream);
   Workspace w = carve(p->workspace, p->batch, p->total_tokens, p->heads);
   // Small batches work out the tile list in the forward kernel (SELF): one lane per sequence,
-  // and every item resident from the start (4 workgroups per compute unit), where the list's
-  // order does not matter.
+  // and every item resident from the start (4 workgroups per compute unit).  The order still
+  // decides which items share a compute unit, so it is the list's once there are more items than
+  // compute units (fwd64_kernel.h has the figures).
   const bool self = da.thr == 0 && !(p->flags & FMHA_FLAG_REUSE_SCHEDULE) && p->batch <= fmha::kSelfListBatch &&
                     items_bound(p) <= (int64_t)compute_units() * 4;
   if (!self && (rc = launch_schedule(p, w, st))) return rc;
   a.pb = problem_of(p, w);
   a.list = fmha::ListArgs{p->cu_seqlens, p->seqused, p->batch, (int32_t)tile_capacity(p->batch, p->total_tokens),
-                          w.count, w.list};
+                          items_bound(p) > (int64_t)compute_units(), w.count, w.list};
   a.feed = fmha::FeedArgs{w.feed, 1};
   a.q = static_cast<const uint16_t*>(q);
   a.k = static_cast<const uint16_t*>(k);

@@ -268,16 +268,34 @@ struct Fwd64Item {
 
 constexpr int kSelfListBatch = 64;  // sequences of a batch whose tile list the forward works out itself
 
-// Small batches (SELF): lane i holds sequence i and where its tiles begin, in pack order.
+// Small batches (SELF): each lane holds a sequence and where its tiles begin.
 struct SelfList {
   SchedSeq seq;
   int tiles, first;  // of this lane's sequence
   int total;         // of the batch
 
-  __device__ __forceinline__ void build(const ListArgs& a, int total_tokens) {
+  // Lane i takes the i-th longest sequence, as the tile-list kernel orders them: one ballot and one
+  // exchange per bit of the bucket.
+  __device__ __forceinline__ void sort() {
+    const int lane = lane_id();
+    int id = sched_bucket(seq.nk) * 64 + lane;
+    static_assert(kSchedBuckets == 128, "seven bits");
+#pragma unroll
+    for (int b = 6; b < 13; b++) {
+      const bool one = (id >> b) & 1;
+      const uint64_t ones = __ballot(one);
+      const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(ones >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ones, 0u));
+      id = __builtin_amdgcn_ds_permute(4 * (one ? 64 - __popcll(ones) + below : lane - below), id);
+    }
+    const int from = 4 * (id & 63);
+    seq = SchedSeq{__builtin_amdgcn_ds_bpermute(from, seq.r0), __builtin_amdgcn_ds_bpermute(from, seq.len),
+                   __builtin_amdgcn_ds_bpermute(from, seq.nk)};
+  }
+  __device__ __forceinline__ void build(const ListArgs& a, int total_tokens, bool sorted) {
     const int lane = lane_id();
     seq = SchedSeq{0, 0, 0};
     if (lane < a.batch) seq = sched_seq(a.cu, a.seqused, lane, total_tokens);
+    if (sorted) sort();  // (uniform)
     tiles = seq.len <= 0 ? 0 : (seq.len + kTileRows - 1) / kTileRows;
     int incl = tiles;
 #pragma unroll
@@ -295,27 +313,22 @@ struct SelfList {
     return TileItem{__builtin_amdgcn_readlane(seq.r0, l), __builtin_amdgcn_readlane(seq.len, l),
                     __builtin_amdgcn_readlane(seq.nk, l), (i - __builtin_amdgcn_readlane(first, l)) * kTileRows};
   }
-  // One wavefront: the list as the tile-list kernel leaves it, longest sequences first.
+  // One wavefront, sorted: the list as the tile-list kernel leaves it.
   __device__ __forceinline__ void publish(const ListArgs& a) const {
-    const int lane = lane_id();
-    const int bucket = sched_bucket(seq.nk);
-    int at = 0;
-    for (int i = 0; i < a.batch; i++) {  // uniform
-      const int bi = __builtin_amdgcn_readlane(bucket, i), ti = __builtin_amdgcn_readlane(tiles, i);
-      if (bi < bucket || (bi == bucket && i < lane)) at += ti;
-    }
     for (int t = 0; t < tiles; t++)
-      if (at + t < a.cap) a.list[at + t] = TileItem{seq.r0, seq.len, seq.nk, t * kTileRows};
-    if (lane == 0) *a.count = total;
+      if (first + t < a.cap) a.list[first + t] = TileItem{seq.r0, seq.len, seq.nk, t * kTileRows};
+    if (lane_id() == 0) *a.count = total;
   }
 };
 
 // SELF: for batches so small that every (tile, head) has a workgroup of its own and the time
 // is the chain of launches and memory round trips.  The workgroups work out the tile list
-// themselves, from the prefix sums and in pack order (with everything running at once the
-// order is of no account), instead of waiting for a launch that does; the last workgroup
+// themselves, from the prefix sums, instead of waiting for a launch that does; the last workgroup
 // takes no item and leaves the list and the feed's counters in the workspace for a backward
-// call.  Measured, a call among others: four sequences of 3 .. 128 tokens, two heads, 12.3 us
+// call.  Items are numbered in pack order while each has a compute unit of its own, and longest
+// sequences first beyond, so that the long ones do not share one: 16 heads, two sequences of 1024
+// tokens among 14 short ones, 33 us in pack order where they came to stand 256 items apart, 24 so (26.5
+// with two launches); sorting costs 0.2 us (64 sequences of 120 tokens, 8 heads: 11.1 and 11.25).  Measured, a call among others: four sequences of 3 .. 128 tokens, two heads, 12.3 us
 // with two launches and 9.7 with one; nine of up to 387 tokens, twelve heads, 14.2 and 11.5.
 template <typename T, bool SELF>
 __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArgs a) {
@@ -325,8 +338,9 @@ __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArg
   const int heads = a.pb.heads;
   SelfList self;
   if (SELF) {
-    self.build(a.list, a.pb.total_tokens);
-    if (blockIdx.x == gridDim.x - 1) {
+    const bool publisher = blockIdx.x == gridDim.x - 1;
+    self.build(a.list, a.pb.total_tokens, publisher || a.list.sorted);
+    if (publisher) {
       for (int i = threadIdx.x; i < kFeedWords; i += kF64Threads) a.feed.counters[i] = 0u;
       if (wave == 0) self.publish(a.list);
       return;

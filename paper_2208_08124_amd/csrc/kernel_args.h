@@ -41,6 +41,7 @@ struct ListArgs {
   const int32_t* cu;       // [batch + 1]
   const int32_t* seqused;  // [batch] or null
   int32_t batch, cap;      // at most 64 sequences; room in the list
+  int32_t sorted;          // items in the list's order, longest sequences first; 0: in pack order
   int32_t* count;          // the list is still left in the workspace, for the backward
   TileItem* list;
 };

@@ -160,6 +160,32 @@ def test_small_batches_find_their_tiles_in_the_forward(lengths, heads, max_seqle
             assert rel <= G_TOL and fro <= G_TOL
 
 
+@pytest.mark.parametrize("lengths,heads,max_seqlen,used", [
+    ([60] * 7 + [1024] + [1, 0, 129, 60] + [1024] + [17] * 3, 16, 1024, False),   # equal lengths, empty ones, long ones late
+    (list(range(64, 0, -1)), 5, 64, False),        # 64 sequences, 320 items
+    ([30, 0, 500, 500, 31, 2], 16, 0, True),       # the order goes by the keys that are attended
+    ([300, 40, 700, 0, 40], 257, 1, False),        # more items than max_seqlen lets expect
+])
+def test_small_batches_longest_sequences_first(lengths, heads, max_seqlen, used):
+    """With more items than compute units the forward of a small batch numbers them as the
+    tile-list kernel does: every row is computed, with the bits of a forward that reads the list."""
+    b = wl.make_batch(lengths, heads, "f16", seed=91 + len(lengths), backward=False)
+    if used:
+        b["seqused"] = np.array([x if i % 2 else min(x, 40) for i, x in enumerate(lengths)], dtype=np.int32)
+    b["max_seqlen"] = max_seqlen
+    d = DeviceBatch(b, False)
+    d.o.fill_(float("nan"))
+    d.lse.fill_(float("nan"))
+    d.fwd()
+    o, lse = d.o.clone(), d.lse.clone()
+    assert not torch.isnan(o).any() and not torch.isnan(lse).any()
+    d.o.fill_(float("nan"))
+    d.lse.fill_(float("nan"))
+    d.fwd(reuse_schedule=True)
+    assert torch.equal(d.o.view(torch.int16), o.view(torch.int16))
+    assert torch.equal(d.lse.view(torch.int32), lse.view(torch.int32))
+
+
 def test_padded_layout_with_key_mask_matches_packed():
     b = wl.make_batch([5, 130, 64, 1, 77], 2, "f16", seed=11)
     db = run(b, True)
