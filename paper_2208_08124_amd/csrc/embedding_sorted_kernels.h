@@ -193,49 +193,66 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
 
 // One workgroup per chunk in which a run begins that goes on into later chunks: its partial
 // sums are added in chunk order and the row is written.  Where the run ends is found first (the
-// first later chunk that it does not cover whole, all threads looking at a chunk each: a binary
-// search in the sorted indices was a chain of 15 - 19 memory round trips), so that the partial
-// sums - up to a few hundred for the most frequent index of a large batch, and its one
-// workgroup is what the kernel waits for - can then be fetched kEmbCombineAhead at a time and
-// added in order (527340 Zipf-distributed rows of 768: 60 us with four at a time, 22 with
-// sixteen, 18 without the search; 65536 rows 87 -> 81 us in all).
-constexpr int kEmbCombineAhead = 16;
+// first later chunk that it does not cover whole, 128 chunks at a time, by each wavefront for
+// itself), so that the partial sums - up to a few hundred for the most frequent index of a large
+// batch, and its one workgroup is what the kernel waits for - can then be fetched kEmbCombineAhead
+// at a time and added in order (527340 Zipf-distributed rows of 768: 60 us with four at a time
+// behind a binary search for the end, 18 so).  Runs of few partial sums, the usual ones of a uniform
+// distribution, fetch no more than kEmbCombineFew: 65536 rows of 128, 8192 indices, both
+// kernels, 15.5 us without that and with the end agreed on in LDS, 13.8 so.
+constexpr int kEmbCombineAhead = 16, kEmbCombineFew = 4;
 template <bool BF16>
 __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbSortedArgs a, const int chunk) {
-  __shared__ int s_last;
-  const int c = blockIdx.x;
+  const int c = blockIdx.x, lane = threadIdx.x & 63;
   const int key = a.info[c].tail_key;
   if (key < 0) return;
   const int chunks = (a.rows - 1) / chunk + 1;
-  if (threadIdx.x == 0) s_last = chunks;
-  __syncthreads();
-  for (int d0 = c + 1;; d0 += kEmbSortThreads) {
-    const int d = min(d0 + (int)threadIdx.x, chunks - 1);  // (a run ends in the last chunk at the latest)
-    if (!a.info[d].head_whole) atomicMin(&s_last, d);
-    __syncthreads();
-    const bool found = s_last < chunks;
-    __syncthreads();
-    if (found) break;
+  int d_last;
+  for (int d0 = c + 1;; d0 += 128) {  // (a run ends in the last chunk at the latest)
+    const uint64_t near = __ballot(!a.info[min(d0 + lane, chunks - 1)].head_whole);
+    const uint64_t far = __ballot(!a.info[min(d0 + 64 + lane, chunks - 1)].head_whole);
+    if (near | far) {
+      d_last = min(d0 + (near ? __builtin_ctzll(near) : 64 + __builtin_ctzll(far)), chunks - 1);
+      break;
+    }
   }
-  const int d_last = s_last;
   const int hidden = 2 * a.pairs;
   uint16_t* dw = reinterpret_cast<uint16_t*>(a.dw);
   for (int col = 8 * threadIdx.x; col < hidden; col += 8 * kEmbSortThreads) {
     const float4* p = reinterpret_cast<const float4*>(a.partial + ((int64_t)c * 2 + 1) * hidden + col);
     float s[8] = {p[0].x, p[0].y, p[0].z, p[0].w, p[1].x, p[1].y, p[1].z, p[1].w};
-    for (int d0 = c + 1; d0 <= d_last; d0 += kEmbCombineAhead) {
-      float4 t[kEmbCombineAhead][2];
+    // (both forms written out: as one function of the number the longer one took 2 - 7 % more)
+    if (d_last - c <= kEmbCombineFew) {
+      const int d0 = c + 1;
+      float4 t[kEmbCombineFew][2];
 #pragma unroll
-      for (int u = 0; u < kEmbCombineAhead; u++) {
+      for (int u = 0; u < kEmbCombineFew; u++) {
         const float4* q = reinterpret_cast<const float4*>(a.partial + (int64_t)min(d0 + u, d_last) * 2 * hidden + col);
         t[u][0] = q[0];
         t[u][1] = q[1];
       }
 #pragma unroll
-      for (int u = 0; u < kEmbCombineAhead; u++) {
+      for (int u = 0; u < kEmbCombineFew; u++) {
         if (d0 + u <= d_last) {
           s[0] += t[u][0].x, s[1] += t[u][0].y, s[2] += t[u][0].z, s[3] += t[u][0].w;
           s[4] += t[u][1].x, s[5] += t[u][1].y, s[6] += t[u][1].z, s[7] += t[u][1].w;
+        }
+      }
+    } else {
+      for (int d0 = c + 1; d0 <= d_last; d0 += kEmbCombineAhead) {
+        float4 t[kEmbCombineAhead][2];
+#pragma unroll
+        for (int u = 0; u < kEmbCombineAhead; u++) {
+          const float4* q = reinterpret_cast<const float4*>(a.partial + (int64_t)min(d0 + u, d_last) * 2 * hidden + col);
+          t[u][0] = q[0];
+          t[u][1] = q[1];
+        }
+#pragma unroll
+        for (int u = 0; u < kEmbCombineAhead; u++) {
+          if (d0 + u <= d_last) {
+            s[0] += t[u][0].x, s[1] += t[u][0].y, s[2] += t[u][0].z, s[3] += t[u][0].w;
+            s[4] += t[u][1].x, s[5] += t[u][1].y, s[6] += t[u][1].z, s[7] += t[u][1].w;
+          }
         }
       }
     }

@@ -169,6 +169,72 @@ def test_sorted_variant_at_the_edges_of_the_sort(t, vocab):
     assert np.array_equal(got, sorted_order_reference(dy_bits, ids, vocab, "f16", 32))
 
 
+def sorted_order_reference_of_one_piece(dy_bits, ids, vocab, dtype, chunk):
+    """sorted_order_reference for dy with eight columns, vectorised over the runs: all runs of a
+    chunk add their r-th row at once, then all weight rows their c-th partial sum."""
+    x = wl.bits_to_f64(dy_bits, dtype).astype(np.float32)
+    key = np.where((ids >= 0) & (ids < vocab), ids, vocab)
+    order = np.argsort(key, kind="stable")
+    key = key[order]
+    at = np.arange(len(key))
+    first = np.ones(len(key), bool)
+    first[1:] = (key[1:] != key[:-1]) | (at[1:] % chunk == 0)
+    part, start = np.cumsum(first) - 1, at[first]
+    sums = np.zeros((len(start), 8), np.float32)
+    r = at - start[part]
+    for i in range(r.max() + 1):
+        sums[part[r == i]] += x[order[r == i]]
+    part_key = key[start]
+    new = np.ones(len(start), bool)
+    new[1:] = part_key[1:] != part_key[:-1]
+    run = np.cumsum(new) - 1
+    c = np.arange(len(start)) - np.flatnonzero(new)[run]
+    out = np.zeros((vocab + 1, 8), np.float32)
+    for i in range(c.max() + 1):
+        out[part_key[c == i]] += sums[c == i]
+    return wl.to_bits(out[:vocab], dtype)
+
+
+@pytest.mark.parametrize("t,vocab", [(131071, 30522), (131072, 30522), (524288, 30522), (524289, 30522), (527340, 30522),
+                                     (527340, 300), (6000, 65535), (6000, 65536), (6000, 1 << 20), (70000, 1 << 20),
+                                     (262143, 100000)])
+def test_sorted_variant_of_many_rows_bit_for_bit(t, vocab):
+    """Chunks of 256 entries from 2^17 rows on, more than 256 tiles (their counts are summed in
+    pieces of 256), digits of 8 and of 10 bits, weight rows cleared ahead of the sums and beside
+    them, a run of more than 128 chunks."""
+    rng = np.random.default_rng(t + vocab)
+    dy_bits = wl.to_bits(rng.standard_normal((t, 8)).astype(np.float32), "bf16")
+    ids = wl.zipf_token_ids(t, min(vocab, 70000), 3).astype(np.int32)
+    ids = np.where(ids < 60, ids, vocab - 1 - ids % vocab).astype(np.int32)   # both ends of the vocabulary
+    ids[::17] = -1
+    ids[5::19] = vocab
+    ws = torch.empty(fmha.fmha_embedding_sort_workspace_size(t, 8), dtype=torch.uint8, device="cuda")
+    fmha.fmha_embedding_sort(torch.from_numpy(ids).cuda(), 8, vocab, ws)
+    dw = torch.full((vocab, 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    fmha.fmha_embedding_bwd_sorted(to_dev(dy_bits, "bf16"), ws, dw, zero_first=True)
+    got = dw.view(torch.int16).cpu().numpy().view(np.uint16)
+    want = sorted_order_reference_of_one_piece(dy_bits, ids, vocab, "bf16", 256 if t >= 1 << 17 else 32)
+    assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n", [1032, 2048])
+@pytest.mark.parametrize("init", [False, True])
+def test_sorted_variant_of_wide_rows_bit_for_bit(n, init):
+    """More columns than a workgroup's threads take at once, with runs over one to forty chunks
+    and weight rows that no index names."""
+    t, vocab = 2500, 90
+    rng = np.random.default_rng(n)
+    dy_bits = wl.to_bits(rng.standard_normal((t, n)).astype(np.float32), "f16")
+    ids = (3 * np.minimum(rng.geometric(0.5, t) - 1, 29)).astype(np.int32)
+    w0 = wl.to_bits(rng.standard_normal((vocab, n)).astype(np.float32), "f16") if init else None
+    ws = torch.empty(fmha.fmha_embedding_sort_workspace_size(t, n), dtype=torch.uint8, device="cuda")
+    fmha.fmha_embedding_sort(torch.from_numpy(ids).cuda(), n, vocab, ws)
+    dw = to_dev(w0, "f16") if init else torch.full((vocab, n), float("nan"), dtype=torch.float16, device="cuda")
+    fmha.fmha_embedding_bwd_sorted(to_dev(dy_bits, "f16"), ws, dw, zero_first=not init)
+    got = dw.view(torch.int16).cpu().numpy().view(np.uint16)
+    assert np.array_equal(got, sorted_order_reference(dy_bits, ids, vocab, "f16", 32, w0))
+
+
 def test_embedding_bwd_argument_errors():
     dy = torch.zeros((4, 12), dtype=torch.float16, device="cuda")
     idx = torch.zeros(4, dtype=torch.int32, device="cuda")
