@@ -41,9 +41,20 @@ SortSpace sort_space(int rows, int hidden) {
   s.sorted = at, at = round_up(at + 8 * n, 256);
   s.info = at, at = round_up(at + sizeof(fmha::EmbChunkInfo) * (size_t)s.chunks, 256);
   s.partial = at, at = round_up(at + sizeof(float) * 2 * (size_t)hidden * (size_t)s.chunks, 256);
-  s.counts = at, at = round_up(at + sizeof(uint32_t) * fmha::kSortDigits * ((size_t)s.tiles + 1), 256);
+  s.counts = at, at = round_up(at + sizeof(uint32_t) * fmha::kSortWideDigits * ((size_t)s.tiles + 1), 256);
   s.bytes = at;
   return s;
+}
+
+template <int DIGITS>
+void sort_pass(const fmha::SortArgs& a, bool sum_in_place, hipStream_t st) {
+  fmha::sort_count_kernel<DIGITS><<<(unsigned)a.tiles, DIGITS, 0, st>>>(a);
+  if (sum_in_place) {
+    fmha::sort_place_kernel<DIGITS, true><<<(unsigned)a.tiles, DIGITS, 0, st>>>(a);
+  } else {
+    fmha::sort_tiles_kernel<DIGITS><<<DIGITS, fmha::kSortTilesThreads, 0, st>>>(a);
+    fmha::sort_place_kernel<DIGITS, false><<<(unsigned)a.tiles, DIGITS, 0, st>>>(a);
+  }
 }
 }  // namespace
 
@@ -67,7 +78,11 @@ extern "C" int fmha_embedding_sort(const int32_t* indices, const int32_t* n_rows
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(workspace);
   uint2* buffers[2] = {reinterpret_cast<uint2*>(w + s.sorted), reinterpret_cast<uint2*>(w + s.moved)};
-  const int key_size = (int)key_bits(vocab), passes = (key_size + 7) / 8;
+  // Digits of at most 8 bits, or of 10 where that saves a pass (position_sort_kernels.h has the figures);
+  // what fits into one workgroup has no launches to save.
+  const int key_size = (int)key_bits(vocab);
+  const bool wide = rows > fmha::kSortSmall && (key_size + 9) / 10 < (key_size + 7) / 8;
+  const int passes = wide ? (key_size + 9) / 10 : (key_size + 7) / 8, digits = wide ? fmha::kSortWideDigits : fmha::kSortDigits;
   fmha::SortArgs a;
   a.indices = indices;
   a.n_rows = n_rows;
@@ -78,7 +93,7 @@ extern "C" int fmha_embedding_sort(const int32_t* indices, const int32_t* n_rows
   a.padding_idx = padding_idx;
   a.tiles = s.tiles;
   const bool sum_in_place = s.tiles <= fmha::kSortSumInPlace;
-  a.tile_stride = sum_in_place ? fmha::kSortDigits : 1;
+  a.tile_stride = sum_in_place ? digits : 1;
   a.digit_stride = sum_in_place ? 1 : s.tiles;
   a.bits = (key_size + passes - 1) / passes;
   if (rows <= fmha::kSortSmall) {
@@ -92,13 +107,10 @@ extern "C" int fmha_embedding_sort(const int32_t* indices, const int32_t* n_rows
     for (int p = 0; p < passes; p++) {
       a.out = buffers[(passes - 1 - p) & 1];  // the last pass writes the result
       a.shift = p * a.bits;
-      fmha::sort_count_kernel<<<(unsigned)s.tiles, fmha::kSortThreads, 0, st>>>(a);
-      if (sum_in_place) {
-        fmha::sort_place_kernel<true><<<(unsigned)s.tiles, fmha::kSortThreads, 0, st>>>(a);
-      } else {
-        fmha::sort_tiles_kernel<<<fmha::kSortDigits, fmha::kSortThreads, 0, st>>>(a);
-        fmha::sort_place_kernel<false><<<(unsigned)s.tiles, fmha::kSortThreads, 0, st>>>(a);
-      }
+      if (wide)
+        sort_pass<fmha::kSortWideDigits>(a, sum_in_place, st);
+      else
+        sort_pass<fmha::kSortDigits>(a, sum_in_place, st);
       a.indices = nullptr;
       a.in = a.out;
     }
