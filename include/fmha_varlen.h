@@ -73,6 +73,8 @@ typedef enum { FMHA_F16 = 0, FMHA_BF16 = 1 } fmha_dtype_t;
 /* fmha_varlen_bwd only: run one of the two backward passes.  The dQ pass also
  * writes the per-row statistics into the workspace; the dK/dV pass reads them,
  * so a dK/dV-only call must follow a dQ pass on the same workspace and inputs.
+ * (The statistics depend on o, d_o and lse alone: the two passes may be given
+ * different dropout, and each applies its own.)
  * The output pointers of the skipped pass are still validated but not written. */
 #define FMHA_FLAG_BWD_ONLY_DQ 2u
 #define FMHA_FLAG_BWD_ONLY_DKV 4u
@@ -220,7 +222,8 @@ int fmha_unpad_indices_host(const int32_t* input_mask, int32_t batch, int32_t se
 
 /* The same on the device: all arrays are device memory (inverse may be NULL), sizes as
  * above; one to three small launches on `stream`, no host synchronisation.  Entries of
- * nonzero_indices at and beyond cu_seqlens[batch] are left alone. */
+ * nonzero_indices at and beyond cu_seqlens[batch] are left alone.  inverse may be
+ * input_mask itself. */
 int fmha_unpad_indices(const int32_t* input_mask, int32_t batch, int32_t seqlen,
                        int32_t* nonzero_indices, int32_t* inverse, int32_t* cu_seqlens,
                        void* stream);

@@ -77,7 +77,7 @@ static __device__ __forceinline__ uint4 emb_finish8(const uint4& old, float (&s)
 // are written whole by their one writer, so clearing all of them ahead of the sums would move
 // most of dw twice and cost a launch: 9 us for 30522 x 768 weights).  A thread looks its row up
 // in the sorted entries by bisection; these workgroups come first in the grid, so that their
-// chains of loads run beside the sums.
+// chains of loads run beside the sums.  (Narrow rows of large vocabularies: see clear_ahead.)
 constexpr int kEmbClearRows = 64;
 static __device__ void emb_clear_rows(const EmbSortedArgs& a, int first, uint32_t* s_absent) {
   const int tid = threadIdx.x, n = min(kEmbClearRows, a.vocab - first);

@@ -12,7 +12,8 @@
 // time, lane l holds columns 1024i + 8l .. +7 and 1024i + 512 + 8l .. +7, so that
 // every load and store instruction covers whole lines (with sixteen columns side
 // by side in a lane each one covers every other 16 bytes: forward and backward of 15769 x 1024 took
-// 70 us, 59 so; of 527340 x 768 1454 us, 1314 so: 4.94 TB/s), every
+// 70 us, 59 so, on rows that have been through the chip before, 76 and 71 on new ones; of 527340 x
+// 768 1454 us, 1312 so: 4.94 TB/s), every
 // statistic is a wavefront reduction, nothing goes through
 // LDS except the once-per-kernel column sums of the backward.  Rows are taken
 // grid-stride by persistent wavefronts so that the column sums live in
