@@ -174,10 +174,16 @@ extern "C" int fmha_embedding_bwd_sorted(const void* dy, void* workspace, size_t
   const unsigned grid = (unsigned)(a.clear + s.chunks);
   if (dtype == FMHA_BF16) {
     fmha::emb_chunk_kernel<true><<<grid, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
-    fmha::emb_combine_kernel<true><<<(unsigned)s.chunks, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
+    if (hidden <= fmha::kEmbCombineNarrow)
+      fmha::emb_combine_kernel<true, true><<<((unsigned)s.chunks + 1) / 2, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
+    else
+      fmha::emb_combine_kernel<true, false><<<(unsigned)s.chunks, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
   } else {
     fmha::emb_chunk_kernel<false><<<grid, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
-    fmha::emb_combine_kernel<false><<<(unsigned)s.chunks, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
+    if (hidden <= fmha::kEmbCombineNarrow)
+      fmha::emb_combine_kernel<false, true><<<((unsigned)s.chunks + 1) / 2, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
+    else
+      fmha::emb_combine_kernel<false, false><<<(unsigned)s.chunks, fmha::kEmbSortThreads, 0, st>>>(a, chunk);
   }
   if ((e = hipGetLastError()) != hipSuccess) return fail(FMHA_ERR_HIP, "sorted embedding backward launch failed: %s", hipGetErrorString(e));
   return FMHA_OK;

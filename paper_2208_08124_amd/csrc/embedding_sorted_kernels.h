@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
   }
 }
 
-// One workgroup per chunk in which a run begins that goes on into later chunks: its partial
+// One workgroup (or wavefront) per chunk in which a run begins that goes on into later chunks: its partial
 // sums are added in chunk order and the row is written.  Where the run ends is found first (the
 // first later chunk that it does not cover whole, 128 chunks at a time, by each wavefront for
 // itself), so that the partial sums - up to a few hundred for the most frequent index of a large
@@ -199,14 +199,18 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_chunk_kernel(const EmbSor
 // at a time and added in order (527340 Zipf-distributed rows of 768: 60 us with four at a time
 // behind a binary search for the end, 18 so).  Runs of few partial sums, the usual ones of a uniform
 // distribution, fetch no more than kEmbCombineFew: 65536 rows of 128, 8192 indices, both
-// kernels, 15.5 us without that and with the end agreed on in LDS, 13.8 so.
-constexpr int kEmbCombineAhead = 16, kEmbCombineFew = 4;
-template <bool BF16>
+// kernels, 15.5 us without that and with the end agreed on in LDS, 13.8 so.  The loads in flight take
+// 154 registers, six workgroups per compute unit: on rows of up to kEmbCombineNarrow columns, which
+// leave one of their two wavefronts idle, each wavefront takes a chunk of its own (500000 rows of 128,
+// uniform over 8192 indices, accumulating: 63.4 us without, 56.3 so; rows of 512 the same either way).
+constexpr int kEmbCombineAhead = 16, kEmbCombineFew = 4, kEmbCombineNarrow = 256;
+template <bool BF16, bool NARROW>
 __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbSortedArgs a, const int chunk) {
-  const int c = blockIdx.x, lane = threadIdx.x & 63;
+  const int chunks = (a.rows - 1) / chunk + 1, lane = threadIdx.x & 63;
+  const int c = NARROW ? 2 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : blockIdx.x;  // (uniform)
+  if (NARROW && c >= chunks) return;
   const int key = a.info[c].tail_key;
   if (key < 0) return;
-  const int chunks = (a.rows - 1) / chunk + 1;
   int d_last;
   for (int d0 = c + 1;; d0 += 128) {  // (a run ends in the last chunk at the latest)
     const uint64_t near = __ballot(!a.info[min(d0 + lane, chunks - 1)].head_whole);
@@ -218,7 +222,7 @@ __global__ __launch_bounds__(kEmbSortThreads) void emb_combine_kernel(const EmbS
   }
   const int hidden = 2 * a.pairs;
   uint16_t* dw = reinterpret_cast<uint16_t*>(a.dw);
-  for (int col = 8 * threadIdx.x; col < hidden; col += 8 * kEmbSortThreads) {
+  for (int col = 8 * (NARROW ? lane : threadIdx.x); col < hidden; col += 8 * kEmbSortThreads) {
     const float4* p = reinterpret_cast<const float4*>(a.partial + ((int64_t)c * 2 + 1) * hidden + col);
     float s[8] = {p[0].x, p[0].y, p[0].z, p[0].w, p[1].x, p[1].y, p[1].z, p[1].w};
     // (both forms written out: as one function of the number the longer one took 2 - 7 % more)

@@ -217,11 +217,12 @@ def test_sorted_variant_of_many_rows_bit_for_bit(t, vocab):
     assert np.array_equal(got, want)
 
 
-@pytest.mark.parametrize("n", [1032, 2048])
+@pytest.mark.parametrize("n", [256, 264, 1032, 2048])
 @pytest.mark.parametrize("init", [False, True])
-def test_sorted_variant_of_wide_rows_bit_for_bit(n, init):
-    """More columns than a workgroup's threads take at once, with runs over one to forty chunks
-    and weight rows that no index names."""
+def test_sorted_variant_by_width_bit_for_bit(n, init):
+    """The widest rows that a wavefront combines by itself, the next, and more columns than a
+    workgroup's threads take at once, with runs over one to forty chunks and weight rows that no
+    index names."""
     t, vocab = 2500, 90
     rng = np.random.default_rng(n)
     dy_bits = wl.to_bits(rng.standard_normal((t, n)).astype(np.float32), "f16")
