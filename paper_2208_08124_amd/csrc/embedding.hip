@@ -2,6 +2,7 @@
 // only) and launches on the caller's stream.  Nothing here allocates, copies to the host or waits.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 
 #include "../../include/fmha_varlen.h"
@@ -52,11 +53,17 @@ SortSpace sort_space(int rows, int hidden) {
 // look up.  Backward with f16 rows, us beside / ahead: 16000 x 128 of 30522 weight rows 17 / 19, of
 // 120000 20.6 / 23.3 (uniform indices 17.7 / 21.2), of 250000 30.9 / 27.6; 40000 x 128 of 120000 29.3 /
 // 26.7, x 256 29.4 / 31.6; 527340 x 128 of 30522 77 / 79, of 120000 104 / 85, x 256 114 / 106, x 512 187 /
-// 181 (uniform 168 / 171), x 768 254 / 279; 300 x 8 of 250000 22.8 / 13.6.
+// 181 (uniform 168 / 171), x 768 254 / 279; 300 x 8 of 250000 22.8 / 13.6.  Where the sums' workgroups fit on
+// the chip at once and only the clearing ones beside them do not, the last sums wait for a second
+// round: 600000 x 128 of 30522 92 / 83 (uniform 79 / 68; x 256 103 / 102 and 89 / 85, left as it is).
+constexpr int64_t kSumsResident = 2560;  // workgroups of the chunk kernel: ten per compute unit
+int64_t clear_groups(int vocab) { return ((int64_t)vocab + fmha::kEmbClearRows - 1) / fmha::kEmbClearRows; }
 bool clear_ahead(int rows, int hidden, int vocab) {
   int64_t steps = 0;
   for (int64_t n = rows; n > 0; n >>= 1) steps += vocab;
-  return steps > 1750000 && hidden < (rows >= (1 << 18) ? 384 : 192);
+  if (steps > 1750000 && hidden < (rows >= (1 << 18) ? 384 : 192)) return true;
+  const int64_t sums = ((int64_t)rows + sort_chunk(rows) - 1) / sort_chunk(rows);
+  return rows >= (1 << 17) && hidden < 192 && sums <= kSumsResident && sums + clear_groups(vocab) > kSumsResident;
 }
 
 template <int DIGITS>
@@ -168,8 +175,7 @@ extern "C" int fmha_embedding_bwd_sorted(const void* dy, void* workspace, size_t
   a.pairs = hidden / 2;
   a.vocab = vocab;
   a.accumulate = (flags & FMHA_EMB_ZERO_FIRST) ? 0 : 1;
-  a.clear = (flags & FMHA_EMB_ZERO_FIRST) && !fill ? (int)(((int64_t)vocab + fmha::kEmbClearRows - 1) / fmha::kEmbClearRows) : 0;
-  if (a.clear > 65536) a.clear = 65536;  // (they stride)
+  a.clear = (flags & FMHA_EMB_ZERO_FIRST) && !fill ? (int)std::min<int64_t>(clear_groups(vocab), 65536) : 0;  // (they stride)
   const int chunk = sort_chunk(rows);
   const unsigned grid = (unsigned)(a.clear + s.chunks);
   if (dtype == FMHA_BF16) {

@@ -197,7 +197,7 @@ def sorted_order_reference_of_one_piece(dy_bits, ids, vocab, dtype, chunk):
 
 @pytest.mark.parametrize("t,vocab", [(131071, 30522), (131072, 30522), (524288, 30522), (524289, 30522), (527340, 30522),
                                      (527340, 300), (6000, 65535), (6000, 65536), (6000, 1 << 20), (70000, 1 << 20),
-                                     (262143, 100000)])
+                                     (262143, 100000), (560000, 30522)])
 def test_sorted_variant_of_many_rows_bit_for_bit(t, vocab):
     """Chunks of 256 entries from 2^17 rows on, more than 256 tiles (their counts are summed in
     pieces of 256), digits of 8 and of 10 bits, weight rows cleared ahead of the sums and beside
