@@ -274,22 +274,24 @@ struct SelfList {
   int tiles, first;  // of this lane's sequence
   int total;         // of the batch
 
-  // Lane i takes the i-th longest sequence, as the tile-list kernel orders them: one ballot and one
-  // exchange per bit of the bucket.
+  // Lane i takes the i-th longest sequence, as the tile-list kernel orders them.  A lane counts the
+  // lanes ahead of its own bit by bit of the bucket (those whose higher bits are the same and whose
+  // next is zero where its own is one), so that only the sequences themselves change lanes.
   __device__ __forceinline__ void sort() {
-    const int lane = lane_id();
-    int id = sched_bucket(seq.nk) * 64 + lane;
+    const int bucket = sched_bucket(seq.nk);
     static_assert(kSchedBuckets == 128, "seven bits");
+    uint64_t same = ~0ull;
+    int rank = 0;
 #pragma unroll
-    for (int b = 6; b < 13; b++) {
-      const bool one = (id >> b) & 1;
+    for (int b = 6; b >= 0; b--) {
+      const bool one = (bucket >> b) & 1;
       const uint64_t ones = __ballot(one);
-      const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(ones >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ones, 0u));
-      id = __builtin_amdgcn_ds_permute(4 * (one ? 64 - __popcll(ones) + below : lane - below), id);
+      rank += one ? __popcll(same & ~ones) : 0;
+      same &= one ? ones : ~ones;
     }
-    const int from = 4 * (id & 63);
-    seq = SchedSeq{__builtin_amdgcn_ds_bpermute(from, seq.r0), __builtin_amdgcn_ds_bpermute(from, seq.len),
-                   __builtin_amdgcn_ds_bpermute(from, seq.nk)};
+    rank += __popcll(same & ((1ull << lane_id()) - 1ull));
+    seq = SchedSeq{__builtin_amdgcn_ds_permute(4 * rank, seq.r0), __builtin_amdgcn_ds_permute(4 * rank, seq.len),
+                   __builtin_amdgcn_ds_permute(4 * rank, seq.nk)};
   }
   __device__ __forceinline__ void build(const ListArgs& a, int total_tokens, bool sorted) {
     const int lane = lane_id();
@@ -328,7 +330,8 @@ struct SelfList {
 // call.  Items are numbered in pack order while each has a compute unit of its own, and longest
 // sequences first beyond, so that the long ones do not share one: 16 heads, two sequences of 1024
 // tokens among 14 short ones, 33 us in pack order where they came to stand 256 items apart, 24 so (26.5
-// with two launches); sorting costs 0.2 us (64 sequences of 120 tokens, 8 heads: 11.1 and 11.25).  Measured, a call among others: four sequences of 3 .. 128 tokens, two heads, 12.3 us
+// with two launches); where the order is of no account sorting costs nothing that can be measured (64
+// sequences of 120 tokens, 8 heads: 11.1 and 11.0).  Measured, a call among others: four sequences of 3 .. 128 tokens, two heads, 12.3 us
 // with two launches and 9.7 with one; nine of up to 387 tokens, twelve heads, 14.2 and 11.5.
 template <typename T, bool SELF>
 __global__ __launch_bounds__(kF64Threads, 2) void fmha_fwd64_kernel(const FwdArgs a) {
