@@ -201,15 +201,14 @@ def main():
     sec = timed(cold_step, args.steps, max(args.warmup, n_sets))
     step_events = dict(timed.events_ms)
 
-    # per-kernel durations: HIP events on the launch stream between the three kernels of a
-    # step (forward with the tile list already built, dQ pass, dK/dV pass), in step order and
+    # per-kernel durations: HIP events on the launch stream between the kernels of a
+    # step (forward with the tile list already built, backward), in step order and
     # rotating over the buffer sets like the timed region, so every kernel sees the cache
     # state it has inside a step
     def kernel_times(steps):
         # the plain forward and the one with dropout are different kernels
         fwd_name = "fmha_fwd64_kernel" if Dev.drop is None else "fmha_fwd_kernel"
-        legs = [(fwd_name, lambda x: x.fwd(reuse=True)), ("bwd_dq_kernel", lambda x: x.bwd(only="dq")),
-                ("bwd_dkv_kernel", lambda x: x.bwd(only="dkv"))]
+        legs = [(fwd_name, lambda x: x.fwd(reuse=True)), ("bwd_fused_kernel", lambda x: x.bwd())]
         evs = [[torch.cuda.Event(enable_timing=True) for _ in range(len(legs) + 1)] for _ in range(steps)]
         for i in range(n_sets):
             sets[i].step()
@@ -238,7 +237,7 @@ def main():
         x.bwd()
     reuse_sec = timed(reuse_step, args.steps, n_sets)
     # the same cold rotation with every buffer set's step captured once in a HIP graph and
-    # replayed: what the launch gaps between the four kernels of a step cost in eager mode
+    # replayed: what the launch gaps between the kernels of a step cost in eager mode
     graph_replay = None
     try:
         graphs = []
@@ -268,7 +267,7 @@ def main():
                         "value": round(fl_all / dsec / 1e12, 3),
                         "kernels_ms": {k: round(v, 5) for k, v in dk_ms.items()}}
     del sets
-    k_fl = {"fmha_fwd_kernel": fl_fwd, "fmha_fwd64_kernel": fl_fwd, "bwd_dq_kernel": fl_dq, "bwd_dkv_kernel": fl_dkv}
+    k_fl = {"fmha_fwd_kernel": fl_fwd, "fmha_fwd64_kernel": fl_fwd, "bwd_fused_kernel": fl_dq + fl_dkv}
     dom = max(k_ms, key=k_ms.get)
     ach = k_fl[dom] / (k_ms[dom] * 1e-3) / 1e12
     peak = PEAK_TFLOPS[dt]
@@ -292,7 +291,7 @@ def main():
         "config": {"workload": b["name"], "baseline_config": args.config, "sequences": int(b["batch"]),
                    "heads": int(H), "head_dim": 64, "max_seqlen": int(b["max_seqlen"]),
                    "total_tokens": int(T), "sum_len_sq": sum_l2,
-                   "step": "tile-list build + forward + backward (dQ pass, dK/dV pass)"},
+                   "step": "tile-list build + forward + backward"},
         "pct_of_mfma_peak": round(100.0 * fl_all / sec / 1e12 / peak, 2),
         "peak_tflops": peak,
         "tokens_per_s": round(T / sec, 1),

@@ -22,7 +22,8 @@ def sources():
     return [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith(".hip")]
 
 
-ATTENTION_SOURCES = ("fmha_varlen.hip", "fwd64_kernel.h", "fwd_kernel.h", "bwd_kernels.h", "mfma_tiles.h",
+ATTENTION_SOURCES = ("fmha_varlen.hip", "fwd64_kernel.h", "fwd_kernel.h", "bwd_fused_kernel.h",
+                     "bwd_kernels.h", "mfma_tiles.h",
                      "kernel_args.h", "item_feed.h", "schedule.h", "dropout.h")
 
 

@@ -184,14 +184,19 @@ __global__ __launch_bounds__(kThreads, DROP ? 2 : 3) void bwd_dq_kernel(const Bw
       const int64_t tok = r0 + qr;
       const uint16_t* gp = a.d_o + tok * a.do_stride + head * kHeadDim + 8 * g;
       const uint16_t* op = a.o + tok * a.o_stride + head * kHeadDim + 8 * g;
+      // (channels by fours, then a tree over the sixteen: the order in which the one-pass kernel
+      // sums as well, so that both hand the dK/dV products the same D)
+      float part[4];
 #pragma unroll
       for (int t = 0; t < 4; t++) {
         gb[t] = *reinterpret_cast<const u32x4*>(gp + 16 * t);
         const u32x4 ov = *reinterpret_cast<const u32x4*>(op + 16 * t);
-#pragma unroll
-        for (int e = 0; e < 4; e++) dsum = Op<T>::dot2(gb[t][e], ov[e], dsum);
+        part[t] = Op<T>::dot2(gb[t][1], ov[1], Op<T>::dot2(gb[t][0], ov[0], 0.f)) +
+                  Op<T>::dot2(gb[t][3], ov[3], Op<T>::dot2(gb[t][2], ov[2], 0.f));
       }
-      dsum += other_half(dsum);
+#pragma unroll
+      for (int t = 0; t < 4; t++) part[t] += other_half(part[t]);
+      dsum = (part[0] + part[1]) + (part[2] + part[3]);
       const int64_t si = (int64_t)head * a.pb.total_tokens + tok;
       lse2 = a.lse[si] * kLog2e;
     }
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(kThreads, DROP ? 2 : 3) void bwd_dq_kernel(const Bw
       const int row = ti.row0 + 32 * wave + (le & 31);
       if (row < len && le < 32) {
         const int64_t si = (int64_t)head * a.pb.total_tokens + r0 + row;
-        a.dsum[si] = dsum;
+        a.dsum[si] = -dsum;
         a.lse2[si] = lse2;
       }
     }
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(kThreads, DROP ? 2 : 3) void bwd_dq_kernel(const Bw
 struct DkvStage {
   uint16_t q[kTileElems];   // 64 queries x 64 channels, swizzled
   uint16_t g[kTileElems];   // dO, same
-  float stat[4][64];        // [0] = LSE*log2(e), [1] = D of the 64 queries; [2], [3] unused
+  float stat[4][64];        // [0] = LSE*log2(e), [1] = -D of the 64 queries; [2], [3] unused
 };
 
 // One block of 32 queries (rows 32*qb.. of the stage) for one wavefront (32 keys).
@@ -323,10 +328,10 @@ __device__ __forceinline__ void dkv_block(f32x16 (&dk)[2], f32x16 (&dv)[2], cons
       if (DROP) {
         const bool on = kept(kb8, 4 * j + e, drop.thr);
         p[4 * j + e] = on ? pe : 0.f;
-        ds[4 * j + e] = pe * ((on ? dp[4 * j + e] * drop.rp : 0.f) - dvv[e]);
+        ds[4 * j + e] = pe * ((on ? dp[4 * j + e] * drop.rp : 0.f) + dvv[e]);
       } else {
         p[4 * j + e] = pe;
-        ds[4 * j + e] = pe * (dp[4 * j + e] - dvv[e]);
+        ds[4 * j + e] = pe * (dp[4 * j + e] + dvv[e]);
       }
     }
   }

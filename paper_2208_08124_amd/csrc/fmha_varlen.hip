@@ -11,6 +11,7 @@
 
 #include "../../include/fmha_varlen.h"
 #include "host_error.h"
+#include "bwd_fused_kernel.h"
 #include "bwd_kernels.h"
 #include "fwd64_kernel.h"
 #include "fwd_kernel.h"
@@ -50,8 +51,13 @@ struct Workspace {
   fmha::TileItem* list;
   float* dsum;
   float* lse2;
-  size_t count_off, feed_off, list_off, dsum_off, lse2_off, bytes_fwd, bytes_bwd;
+  fmha::TileItem* seqs;  // the sequences, for the one-pass backward
+  float* slab;           // its fp32 dQ between sweeps
+  size_t count_off, feed_off, list_off, seqs_off, dsum_off, lse2_off, slab_off, bytes_list, bytes_fwd, bytes_bwd;
 };
+
+// Workgroups of the one-pass backward, and rows of fp32 dQ that each may be given.
+constexpr int64_t kFusedGrid = 256, kFusedSlabRows = 2048;
 
 Workspace carve(void* base, int64_t batch, int64_t total_tokens, int64_t heads) {
   Workspace w;
@@ -59,12 +65,21 @@ Workspace carve(void* base, int64_t batch, int64_t total_tokens, int64_t heads) 
   w.feed_off = kAlign;
   w.list_off = w.feed_off + sizeof(uint32_t) * fmha::kFeedWords;
   const size_t list_bytes = sizeof(fmha::TileItem) * (size_t)(tile_capacity(batch, total_tokens) + 1);
-  w.dsum_off = round_up(w.list_off + list_bytes, kAlign);
+  w.bytes_list = w.list_off + list_bytes;
+  w.seqs_off = round_up(w.bytes_list, kAlign);
+  w.dsum_off = round_up(w.seqs_off + sizeof(fmha::TileItem) * (size_t)batch, kAlign);
   w.bytes_fwd = w.dsum_off;
   // one float per (token, head) plus one pad entry
   const size_t stat_bytes = round_up(sizeof(float) * ((size_t)total_tokens * (size_t)heads + 1), kAlign);
   w.lse2_off = w.dsum_off + stat_bytes;
-  w.bytes_bwd = w.lse2_off + stat_bytes;
+  // dQ between sweeps: a workgroup needs no more rows than a sequence has, and there are no more
+  // workgroups on long sequences than there are rows in all heads
+  w.slab_off = w.lse2_off + stat_bytes;
+  const int64_t rows = ((int64_t)total_tokens + 255) / 256 * 256;
+  int64_t slab = kFusedGrid * (rows < kFusedSlabRows ? rows : kFusedSlabRows);
+  if (slab > rows * heads) slab = rows * heads;
+  if (total_tokens <= fmha::kFusedKeys) slab = 0;
+  w.bytes_bwd = w.slab_off + (size_t)slab * fmha::kHeadDim * sizeof(float);
   // (base is null when only the sizes are wanted: no pointer arithmetic on it then)
   const uintptr_t b = reinterpret_cast<uintptr_t>(base);
   auto at = [b](size_t off) { return b ? reinterpret_cast<void*>(b + off) : nullptr; };
@@ -73,6 +88,8 @@ Workspace carve(void* base, int64_t batch, int64_t total_tokens, int64_t heads) 
   w.list = static_cast<fmha::TileItem*>(at(w.list_off));
   w.dsum = static_cast<float*>(at(w.dsum_off));
   w.lse2 = static_cast<float*>(at(w.lse2_off));
+  w.seqs = static_cast<fmha::TileItem*>(at(w.seqs_off));
+  w.slab = static_cast<float*>(at(w.slab_off));
   return w;
 }
 
@@ -88,7 +105,7 @@ int check_stride(const char* name, int64_t s, int64_t dense, int64_t* out) {
   return FMHA_OK;
 }
 
-int check_common(const fmha_varlen_params_t* p, bool bwd) {
+int check_common(const fmha_varlen_params_t* p, bool bwd, bool list_only = false) {
   if (!p) return fail(FMHA_ERR_INVALID_ARG, "params is null");
   if (p->head_dim != fmha::kHeadDim) return fail(FMHA_ERR_UNSUPPORTED, "head_dim=%d, only 64 is supported", p->head_dim);
   if (p->dtype != FMHA_F16 && p->dtype != FMHA_BF16) return fail(FMHA_ERR_UNSUPPORTED, "dtype=%d is neither FMHA_F16 nor FMHA_BF16", p->dtype);
@@ -111,7 +128,8 @@ int check_common(const fmha_varlen_params_t* p, bool bwd) {
     if (cu[p->batch] != p->total_tokens)
       return fail(FMHA_ERR_INVALID_ARG, "cu_seqlens_host[batch]=%d differs from total_tokens=%d", cu[p->batch], p->total_tokens);
   }
-  const size_t need = fmha_varlen_workspace_size(p->batch, p->total_tokens, p->heads, bwd);
+  const Workspace sizes = carve(nullptr, p->batch, p->total_tokens, p->heads);
+  const size_t need = list_only ? sizes.bytes_list : bwd ? sizes.bytes_bwd : sizes.bytes_fwd;
   if (!p->workspace) return fail(FMHA_ERR_WORKSPACE, "workspace is null (%zu bytes needed)", need);
   if (misaligned(p->workspace, kAlign)) return fail(FMHA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (p->workspace_bytes < need) return fail(FMHA_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", p->workspace_bytes, need);
@@ -158,8 +176,8 @@ unsigned grid_for(const fmha_varlen_params_t* p, int per_cu) {
 int launch_schedule(const fmha_varlen_params_t* p, const Workspace& w, hipStream_t st) {
   if (p->flags & FMHA_FLAG_REUSE_SCHEDULE) return FMHA_OK;
   const int cap = (int)tile_capacity(p->batch, p->total_tokens);
-  fmha::schedule_kernel<<<1, fmha::kSchedThreads, 0, st>>>(p->cu_seqlens, p->seqused, p->batch, p->total_tokens, w.count,
-                                                          w.list, cap, w.feed);
+  fmha::schedule_kernel<<<w.seqs ? 2 : 1, fmha::kSchedThreads, 0, st>>>(p->cu_seqlens, p->seqused, p->batch, p->total_tokens,
+                                                                       w.count, w.list, cap, w.feed, w.seqs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(FMHA_ERR_HIP, "schedule launch failed: %s", hipGetErrorString(e));
   return FMHA_OK;
@@ -200,6 +218,40 @@ unsigned feed_grid(const fmha_varlen_params_t* p, int per_cu, const Workspace& w
   feed->counters = w.feed;
   feed->chunk = (int32_t)chunk;
   return (unsigned)g;
+}
+
+// Workgroups of the one-pass backward: one per compute unit, a multiple of 8.
+int64_t fused_grid(const fmha_varlen_params_t* p) {
+  const int64_t items = (int64_t)p->batch * p->heads;
+  return ((items < kFusedGrid ? items : kFusedGrid) + 7) / 8 * 8;
+}
+
+// Rows of fp32 dQ for each workgroup of the one-pass backward.
+// (a multiple of 256: the sweeps of a sequence that needs more begin at multiples of eight blocks)
+int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
+  int64_t rows = p->max_seqlen > 0 && p->max_seqlen < p->total_tokens ? p->max_seqlen : p->total_tokens;
+  rows = (rows + 255) / 256 * 256;
+  return (int32_t)(rows < kFusedSlabRows ? rows : kFusedSlabRows);
+}
+
+// Whether the backward runs as one pass (bwd_fused_kernel.h) or as two (bwd_kernels.h).  The one
+// pass is 1.1 - 1.4 times as fast while all compute units are busy, but its items are whole sequences: it
+// is taken where the longest one is at most 1 / 0.6 of a compute unit's share of the work, estimated from
+// below by what the batch would be with all sequences as long (then it is rarely a third longer than
+// its share; two passes have tiles of 128 rows to deal out).  Sequences of up to 64 (128) tokens are
+// taken four (two) heads at a time; with head counts that leave a quarter (fifth) of those places empty the
+// gain there is gone (1097 sequences of up to 109, 2 heads, dropout: 100 us in two passes, 112 in one).
+bool one_pass(const fmha_varlen_params_t* p, const Workspace& w) {
+  if (p->flags & (FMHA_FLAG_BWD_ONLY_DQ | FMHA_FLAG_BWD_ONLY_DKV)) return false;
+  if (p->max_seqlen <= 0) return false;
+  const int h = p->heads;
+  if (p->max_seqlen <= 128 && (h < 0.8 * ((h + 1) / 2 * 2) || h < 0.75 * ((h + 3) / 4 * 4))) return false;
+  const size_t slab = (size_t)fused_grid(p) * (size_t)fused_slab_rows(p) * fmha::kHeadDim * sizeof(float);
+  if (p->max_seqlen > fmha::kFusedKeys && w.bytes_bwd - w.slab_off < slab) return false;
+  // in steps of 256 keys by 32 queries
+  const double longest = (double)((p->max_seqlen + 255) / 256) * ((p->max_seqlen + 31) / 32);
+  const double share = (double)p->total_tokens * p->total_tokens * h / ((double)p->batch * 256 * 32 * kFusedGrid);
+  return share >= 0.6 * longest;
 }
 
 // Dropout arguments for the kernels; d == nullptr means no dropout.
@@ -244,7 +296,7 @@ int static_scratch(void** out) {
 }
 
 int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dropout, const void* q,
-            const void* k, const void* v, void* o, float* lse, void* stream);
+            const void* k, const void* v, void* o, float* lse, void* stream, bool list_only = false);
 int run_bwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dropout, const void* q,
             const void* k, const void* v, const void* o, const void* d_o, const float* lse, void* dq,
             void* dk, void* dv, void* stream);
@@ -288,7 +340,7 @@ int fmha_varlen_fwd_static(const fmha_varlen_params_t* p, const void* q, const v
   if (!p) return fail(FMHA_ERR_INVALID_ARG, "params is null");
   if (p->batch < 0 || p->total_tokens < 0 || p->heads <= 0)
     return fail(FMHA_ERR_INVALID_ARG, "batch=%d, total_tokens=%d, heads=%d: invalid sizes", p->batch, p->total_tokens, p->heads);
-  const size_t need = fmha_varlen_workspace_size(p->batch, p->total_tokens, p->heads, 0);
+  const size_t need = carve(nullptr, p->batch, p->total_tokens, p->heads).bytes_list;
   if (need > kStaticScratchBytes)
     return fail(FMHA_ERR_WORKSPACE,
                 "a batch of %d sequences and %d tokens needs %zu bytes for its tile list, the built-in scratch "
@@ -300,7 +352,7 @@ int fmha_varlen_fwd_static(const fmha_varlen_params_t* p, const void* q, const v
   fmha_varlen_params_t local = *p;
   local.workspace = ptr;
   local.workspace_bytes = kStaticScratchBytes;
-  return run_fwd(&local, nullptr, false, q, k, v, o, lse, stream);
+  return run_fwd(&local, nullptr, false, q, k, v, o, lse, stream, true);
 }
 
 int fmha_varlen_bwd(const fmha_varlen_params_t* p, const void* q, const void* k, const void* v,
@@ -346,8 +398,8 @@ int fmha_dropout_keep_mask(const fmha_varlen_params_t* p, const fmha_dropout_t* 
 namespace {
 
 int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dropout, const void* q,
-            const void* k, const void* v, void* o, float* lse, void* stream) {
-  int rc = check_common(p, false);
+            const void* k, const void* v, void* o, float* lse, void* stream, bool list_only) {
+  int rc = check_common(p, false, list_only);
   if (rc) return rc;
   fmha::DropArgs da;
   if ((rc = drop_args(d, with_dropout, &da))) return rc;
@@ -365,6 +417,7 @@ int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   if (p->batch == 0 || p->total_tokens == 0) return FMHA_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   Workspace w = carve(p->workspace, p->batch, p->total_tokens, p->heads);
+  if (list_only) w.seqs = nullptr;  // (no backward follows)
   // Small batches work out the tile list in the forward kernel (SELF): one lane per sequence,
   // and every item resident from the start (4 workgroups per compute unit).  The order still
   // decides which items share a compute unit, so it is the list's once there are more items than
@@ -374,7 +427,7 @@ int run_fwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   if (!self && (rc = launch_schedule(p, w, st))) return rc;
   a.pb = problem_of(p, w);
   a.list = fmha::ListArgs{p->cu_seqlens, p->seqused, p->batch, (int32_t)tile_capacity(p->batch, p->total_tokens),
-                          items_bound(p) > (int64_t)compute_units(), w.count, w.list};
+                          items_bound(p) > (int64_t)compute_units(), w.count, w.list, w.seqs};
   a.feed = fmha::FeedArgs{w.feed, 1};
   a.q = static_cast<const uint16_t*>(q);
   a.k = static_cast<const uint16_t*>(k);
@@ -451,6 +504,26 @@ int run_bwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   a.dq = static_cast<uint16_t*>(dq);
   a.dk = static_cast<uint16_t*>(dk);
   a.dv = static_cast<uint16_t*>(dv);
+  if (one_pass(p, w)) {
+    const int64_t grid = fused_grid(p);
+    a.seqs = w.seqs;
+    a.slab = w.slab;
+    a.slab_rows = fused_slab_rows(p);
+    if (da.thr == 0) {
+      if (p->dtype == FMHA_F16)
+        fmha::bwd_fused_kernel<_Float16, false><<<(unsigned)grid, fmha::kFusedThreads, 0, st>>>(a);
+      else
+        fmha::bwd_fused_kernel<__bf16, false><<<(unsigned)grid, fmha::kFusedThreads, 0, st>>>(a);
+    } else {
+      if (p->dtype == FMHA_F16)
+        fmha::bwd_fused_kernel<_Float16, true><<<(unsigned)grid, fmha::kFusedThreads, 0, st>>>(a);
+      else
+        fmha::bwd_fused_kernel<__bf16, true><<<(unsigned)grid, fmha::kFusedThreads, 0, st>>>(a);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(FMHA_ERR_HIP, "backward launch failed: %s", hipGetErrorString(e));
+    return FMHA_OK;
+  }
   // persistent grids with their own hand-out chunk sizes: 3 workgroups per compute unit for
   // the dQ pass (2 with dropout), 2 for the dK/dV pass
   fmha::BwdArgs a_dq = a, a_dkv = a;

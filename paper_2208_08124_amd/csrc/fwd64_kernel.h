@@ -320,6 +320,18 @@ struct SelfList {
     for (int t = 0; t < tiles; t++)
       if (first + t < a.cap) a.list[first + t] = TileItem{seq.r0, seq.len, seq.nk, t * kTileRows};
     if (lane_id() == 0) *a.count = total;
+    if (!a.seqs) return;
+    // the list of sequences, in the same order
+    const int b = sched_bucket(seq.nk);
+    const uint64_t live = __ballot(seq.len > 0);
+    const int all = __popcll(live);
+    const int pairs = __popcll(live & __ballot(b < kSchedPairs)), quads = __popcll(live & __ballot(b < kSchedQuads));
+    if (seq.len > 0) a.seqs[__popcll(live & ((1ull << lane_id()) - 1ull))] = TileItem{seq.r0, seq.len, seq.nk, 0};
+    if (lane_id() == 0) {
+      a.count[1] = a.seqused ? all : pairs;
+      a.count[2] = a.seqused ? 0 : quads - pairs;
+      a.count[3] = a.seqused ? 0 : all - quads;
+    }
   }
 };
 

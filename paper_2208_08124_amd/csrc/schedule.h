@@ -33,18 +33,30 @@ __device__ __forceinline__ SchedSeq sched_seq(const int32_t* __restrict__ cu, co
   return s;
 }
 
-// One workgroup.  count <- number of tiles, list[0..count) <- tiles.  `cap`
-// bounds the list (total_tokens/128 + batch always suffices).
+// The one-pass backward (bwd_fused_kernel.h) takes whole sequences, and several heads of short
+// ones at once: four of sequences in buckets from kSchedQuads on (up to 64 keys), two in those from
+// kSchedPairs on (up to 128).  The sequences are listed in the order of the tiles' buckets, so the
+// kinds follow one another.  (With key counts of their own - seqused - a sequence of few keys may
+// have many queries: then all are taken one head at a time.)
+constexpr int kSchedPairs = kSchedBuckets - 1 - 16, kSchedQuads = kSchedBuckets - 1 - 8;
+
+// Workgroup 0: count[0] <- number of tiles, list[0..count) <- tiles.  `cap` bounds the list
+// (total_tokens/128 + batch always suffices).  Workgroup 1, if there is one: count[1..3] <- numbers of
+// sequences taken one, two and four heads at a time, seqs[0..) <- the sequences; the same steps with one
+// entry per sequence, at the same time (in one workgroup 0.4 - 1.2 us more at 2000 sequences).
 __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(const int32_t* __restrict__ cu,
                                                                  const int32_t* __restrict__ seqused,
                                                                  int batch, int total_tokens, int32_t* count,
-                                                                 TileItem* list, int cap, uint32_t* feed_counters) {
+                                                                 TileItem* list, int cap, uint32_t* feed_counters,
+                                                                 TileItem* seqs) {
   __shared__ int cursor[kSchedBuckets];
   const int tid = threadIdx.x;
-  if (tid < kFeedWords) feed_counters[tid] = 0u;  // the item feed's counters start at zero
+  const bool of_seqs = blockIdx.x == 1;
+  if (!of_seqs && tid < kFeedWords) feed_counters[tid] = 0u;  // the item feed's counters start at zero
   static_assert(kFeedWords <= kSchedThreads, "one thread per word");
   if (tid < kSchedBuckets) cursor[tid] = 0;
   __syncthreads();
+  auto entries = [&](const SchedSeq& s) { return of_seqs ? 1 : (s.len + kTileRows - 1) / kTileRows; };
   // The thread's first sequence stays in registers for the second sweep (one memory
   // round trip less on the usual batch of at most 1024 sequences).
   SchedSeq first = {0, 0, 0};
@@ -52,7 +64,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(const int32_t* 
     const SchedSeq s = sched_seq(cu, seqused, i, total_tokens);
     if (i == tid) first = s;
     if (s.len <= 0) continue;
-    atomicAdd(&cursor[sched_bucket(s.nk)], (s.len + kTileRows - 1) / kTileRows);
+    atomicAdd(&cursor[sched_bucket(s.nk)], entries(s));
   }
   __syncthreads();
   // exclusive prefix sum over the 128 buckets: two wavefronts scan 64 each, the
@@ -74,17 +86,30 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(const int32_t* 
   if (tid < kSchedBuckets) {
     const int excl = incl - mine + (tid >= 64 ? half_total : 0);
     cursor[tid] = excl;
-    if (tid == kSchedBuckets - 1) {
-      const int run = excl + mine;
-      *count = run < cap ? run : cap;
+    const int run = excl + mine;
+    if (!of_seqs) {
+      if (tid == kSchedBuckets - 1) *count = run < cap ? run : cap;
+    } else if (tid >= 64) {
+      // (the sequences ahead of a kind's first bucket)
+      static_assert(kSchedPairs >= 64 && kSchedQuads >= 64, "in the second half");
+      const int pairs = __shfl(excl, kSchedPairs - 64, 64), quads = __shfl(excl, kSchedQuads - 64, 64);
+      if (tid == kSchedBuckets - 1) {
+        count[1] = seqused ? run : pairs;
+        count[2] = seqused ? 0 : quads - pairs;
+        count[3] = seqused ? 0 : run - quads;
+      }
     }
   }
   __syncthreads();
   for (int i = tid; i < batch; i += kSchedThreads) {
     const SchedSeq s = i == tid ? first : sched_seq(cu, seqused, i, total_tokens);
     if (s.len <= 0) continue;
-    const int nt = (s.len + kTileRows - 1) / kTileRows;
+    const int nt = entries(s);
     const int at = atomicAdd(&cursor[sched_bucket(s.nk)], nt);
+    if (of_seqs) {
+      seqs[at] = TileItem{s.r0, s.len, s.nk, 0};
+      continue;
+    }
     for (int t = 0; t < nt; t++)
       if (at + t < cap) list[at + t] = TileItem{s.r0, s.len, s.nk, t * kTileRows};
   }

@@ -1,0 +1,112 @@
+"""The backward kernel that forms every score once, against the two passes it stands in for and
+against the oracle.
+
+The library takes it where the batch keeps all compute units busy with whole sequences.  The two
+passes run one after the other (`only`) give the same dV bit for bit (same products in the same order),
+and with dropout the same dK.  The rest differs by what rounds otherwise: dQ sums over keys in another
+order, and without dropout dP - D is summed from -D on, so that a dS = P (dP - D) beside a rounding
+boundary of the 16-bit type may fall on its other side.  One such dS moves a gradient by one unit in
+the last place of dS times K or Q; the bound allows each of a row's dS to do so on average by a
+quarter, in units of the largest gradient of the sequence."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from oracle.parity import G_TOL, gradient_errors
+from paper_2208_08124_amd import workloads as wl
+
+from gpu_util import DeviceBatch, oracle_inputs, to_f64
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 255, 256]
+LONG = EDGES + [257, 287, 288, 300, 384, 385, 511, 512]
+
+
+def fill(some, n):
+    return [some[i % len(some)] for i in range(n)]
+
+
+def both_ways(b, dropout=None):
+    """dQ, dK, dV by one call and by the two passes."""
+    # the batch is one the library takes the kernel for: a compute unit's share of the work (in blocks of
+    # 256 keys by 32 queries, as if all sequences were as long) is at least 0.6 of the longest sequence's
+    n = b["max_seqlen"]
+    assert b["total_tokens"] ** 2 * b["heads"] / (b["batch"] * 8192.0 * 256) >= 0.6 * -(-n // 256) * -(-n // 32)
+    db = DeviceBatch(b, True)
+    db.fwd(dropout=dropout)
+    for x in (db.dq, db.dk, db.dv):
+        x.fill_(float("nan"))
+    db.bwd(reuse_schedule=True, dropout=dropout)
+    one = [x.clone() for x in (db.dq, db.dk, db.dv)]
+    for x in (db.dq, db.dk, db.dv):
+        x.fill_(float("nan"))
+    db.bwd(reuse_schedule=True, dropout=dropout, only="dq")
+    db.bwd(reuse_schedule=True, dropout=dropout, only="dkv")
+    torch.cuda.synchronize()
+    return db, one, [db.dq, db.dk, db.dv]
+
+
+def compare(b, one, two, dtype, dropout=None):
+    assert not any(torch.isnan(x).any() for x in one)
+    assert torch.equal(one[2], two[2])
+    if dropout:
+        assert torch.equal(one[1], two[1])
+    for x, y in zip(one[:2], two[:2]):
+        rel, _ = gradient_errors(to_f64(x), to_f64(y), b["cu_seqlens"])
+        assert rel <= (2.0 ** -9 if dtype == "f16" else 2.0 ** -6), rel
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("lengths,heads,dropout,used", [
+    (fill([1, 31, 32, 33, 64], 300), 16, None, False),       # four heads at a time
+    (fill([3, 64, 17, 64], 400), 13, None, False),               # and a last group of one
+    (fill([65, 96, 97, 128], 150), 15, None, False),         # two at a time, the last alone
+    (fill(EDGES, 140), 16, None, False),                      # all kinds, one sweep each
+    (fill(LONG, 132), 16, None, False),                      # two sweeps
+    (fill(LONG, 110), 16, (0.1, 77), False),
+    (fill(EDGES, 140), 13, (0.25, 5), False),
+    (fill(LONG, 110), 16, None, True),
+    (fill([1025, 700, 1100], 40), 16, None, False)            # up to five,
+])
+def test_one_pass_against_the_two(lengths, heads, dropout, used, dtype):
+    b = wl.make_batch(lengths, heads, dtype, seed=len(lengths) + heads)
+    if used:
+        rng = np.random.default_rng(3)
+        b["seqused"] = np.array([int(rng.integers(0, n + 1)) for n in lengths], dtype=np.int32)
+    db, one, two = both_ways(b, dropout)
+    compare(b, one, two, dtype, dropout)
+    if dropout is None and not used:
+        pick = list(range(0, len(lengths), max(len(lengths) // 7, 1)))
+        cu = b["cu_seqlens"]
+        rows = np.concatenate([np.arange(cu[i], cu[i + 1]) for i in pick])
+        x = {n: v[rows] for n, v in oracle_inputs(b).items() if n in ("q", "k", "v", "do")}
+        sub_cu = wl.cu_from_lengths(np.array([lengths[i] for i in pick]))
+        ref = oracle.bwd(x["q"], x["k"], x["v"], x["do"], sub_cu, b["scale"])
+        for name, got, want in zip(("dq", "dk", "dv"), one, ref):
+            rel, fro = gradient_errors(to_f64(got[torch.from_numpy(rows).cuda()]), want, sub_cu)
+            assert rel <= G_TOL and fro <= G_TOL, f"{name}: {rel:.3e} {fro:.3e}"
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_sequences_longer_than_stated(dtype):
+    """max_seqlen too small: dQ does not fit its buffer, and is formed in sweeps of its own."""
+    b = wl.make_batch(fill([40, 256, 64, 129], 130) + [700, 300, 1030], 12, dtype, seed=9)
+    b["max_seqlen"] = 256
+    db, one, two = both_ways(b)
+    compare(b, one, two, dtype)
+
+
+def test_repeats_itself_and_leaves_the_statistics_of_the_two_passes():
+    b = wl.make_batch(fill(LONG, 132), 16, "f16", seed=4)
+    db, one, two = both_ways(b)
+    two_dk = two[1].clone()
+    db.bwd(reuse_schedule=True)
+    again = [x.clone() for x in (db.dq, db.dk, db.dv)]
+    db.dk.fill_(float("nan"))
+    db.bwd(reuse_schedule=True, only="dkv")    # with what the call before left in the workspace
+    torch.cuda.synchronize()
+    for x, y in zip(one, again):
+        assert torch.equal(x, y)
+    assert torch.equal(db.dk, two_dk)
