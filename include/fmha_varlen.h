@@ -39,7 +39,7 @@
  *     the probabilities are rounded to the operand type before they are
  *     multiplied with V (and dO), as is dS before it meets K and Q.
  *   - The workspace carries state from the forward to the backward call and
- *     between the two backward passes: calls that may overlap in time (other
+ *     between the backward's passes: calls that may overlap in time (other
  *     streams, other threads) need workspaces of their own.  The library keeps
  *     no other state, so such calls are safe.
  *   - Errors are return codes; fmha_last_error() gives a message for the last
@@ -65,14 +65,16 @@ typedef enum {
 
 typedef enum { FMHA_F16 = 0, FMHA_BF16 = 1 } fmha_dtype_t;
 
-/* The workspace already holds the tile list for exactly this cu_seqlens /
- * seqused / batch: skip rebuilding it.  A training step calls attention once
+/* The workspace already holds the tile list (and the list of sequences beside it) for
+ * exactly this cu_seqlens / seqused / batch: skip rebuilding it.  A training step calls attention once
  * per layer and direction with the same batch, as the paper computes its
  * batch_offset once per mini-batch (Section IV-B-2). */
 #define FMHA_FLAG_REUSE_SCHEDULE 1u
-/* fmha_varlen_bwd only: run one of the two backward passes.  The dQ pass also
+/* fmha_varlen_bwd only: run one half of the backward as a pass by itself.  (With neither flag
+ * the library takes one pass that forms the scores once, or both of these, by the sizes of
+ * the batch; either way the statistics are left behind.)  The dQ pass also
  * writes the per-row statistics into the workspace; the dK/dV pass reads them,
- * so a dK/dV-only call must follow a dQ pass on the same workspace and inputs.
+ * so a dK/dV-only call must follow a dQ pass (or a whole backward) on the same workspace and inputs.
  * (The statistics depend on o, d_o and lse alone: the two passes may be given
  * different dropout, and each applies its own.)
  * The output pointers of the skipped pass are still validated but not written. */
@@ -85,8 +87,8 @@ typedef struct fmha_varlen_params {
   int32_t heads;        /* H >= 1 */
   int32_t head_dim;     /* must be 64 */
   int32_t max_seqlen;   /* upper bound on the longest sequence, or <= 0 if unknown.  It only
-                           sizes the launch (the kernels stride over the tile list, so a
-                           wrong value costs time, not correctness); a value smaller than a
+                           sizes the launch and chooses the backward's kernel (the kernels stride
+                           over the lists, so a wrong value costs time, not correctness); a value smaller than a
                            length seen in cu_seqlens_host is reported as an error */
   int32_t dtype;        /* fmha_dtype_t */
   uint32_t flags;       /* FMHA_FLAG_* */
@@ -104,9 +106,10 @@ typedef struct fmha_varlen_params {
   size_t workspace_bytes;
 } fmha_varlen_params_t;
 
-/* Bytes of device workspace for a batch of this shape (tile list; plus, if
+/* Bytes of device workspace for a batch of this shape (tile list, list of sequences; plus, if
  * need_bwd, two fp32 per (token, head): the row sums of dO o O and the
- * log-sum-exp in base-2 units).  Pure host arithmetic; returns 0 on invalid sizes. */
+ * log-sum-exp in base-2 units, and fp32 dQ of the sequences under way: up to 2048 rows of 256
+ * bytes for each of at most 256 workgroups, 128 MiB, none for batches of up to 256 tokens).  Pure host arithmetic; returns 0 on invalid sizes. */
 size_t fmha_varlen_workspace_size(int32_t batch, int32_t total_tokens, int32_t heads,
                                   int32_t need_bwd);
 
@@ -126,7 +129,8 @@ int fmha_varlen_fwd(const fmha_varlen_params_t* p, const void* q, const void* k,
  * hipMalloc / hipFree and calls no allocating routine.  p->workspace and
  * p->workspace_bytes are ignored; everything else (arguments, results, error codes) is as
  * for fmha_varlen_fwd, whose kernels it shares.
- *   - Limit: fmha_varlen_workspace_size(batch, total_tokens, heads, 0) must not exceed
+ *   - Limit: the tile list (16 bytes per tile of 128 rows, counted as total_tokens / 128 + batch,
+ *     and the counters ahead of it) must not exceed
  *     fmha_varlen_static_scratch_bytes() (1 MiB: about 65 000 tiles); larger batches are
  *     rejected with FMHA_ERR_WORKSPACE and nothing is launched.
  *   - Every GPU the library runs on holds its own copy of that array until the process

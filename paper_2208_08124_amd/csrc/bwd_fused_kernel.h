@@ -22,6 +22,18 @@
 // it wrote itself.  (A sequence longer than that buffer, possible only if max_seqlen was stated
 // too small, is done in more sweeps: first dK and dV, then dQ for as many rows as fit at a time.)
 //
+// What bounds it: the issue of instructions.  A step takes about 3400 cycles; of those the matrix cores of a
+// SIMD work 2 x 640 for its two wavefronts, each of which has 24 products, 16 exponentials and about 130
+// other vector instructions to issue beside them (the products of one and the vector instructions of
+// the other hardly overlap), and a sweep has some 17 000 cycles outside its steps (K and V in, operands
+// transposed, the first step, dK and dV out).  So an instruction less per step counts: with the products of
+// dK ahead of those of dV (dS is used up before its successor is packed, without copies), dS in runs that
+// need no XOR per place, and no scratch memory in any instance (a reload waits for all transfers under
+// way), a backward pass of 65 536 tokens and 16 heads took 339 for 361 us at length 256, 262 for 272 at
+// 512, 264 for 288 at 128 and 238 for 257 at 64; with dropout 423 for 492, 353 for 395, 312 for 356, 264 for 313.
+// Two passes / one, 32 768 tokens, 16 heads, us, without and with dropout: length 64 194 / 129, 220 / 144; 128
+// 196 / 147, 219 / 172; 256 242 / 174, 295 / 223; 512 339 / 267, 460 / 368.
+//
 // Every sum is formed in a fixed order: results are identical from run to run.  With dropout dK and dV
 // are those of the two passes bit for bit; without, dP - D is summed from -D on (16 subtractions and 8
 // registers less a step), which rounds otherwise.
@@ -49,13 +61,23 @@ struct FusedLds {
   uint16_t rows[2][2][32 * 64];      // finished dQ of a block (of two heads), on its way out
   float lse[kFusedSlots][64];
   float stat[kFusedSlots][128];      // LSE * log2(e) of 32 rows, -D of 32 rows; the other half takes what lanes without a row write
-  uint32_t mailbox;
+  u32x4 record;   // the next item's sequence
+  int mail[2];    // the next item, and its sequence's place among those of the section
 };
 
 // (referred to as what it is, LDS: an address taken through a generic reference is checked for null)
 typedef __attribute__((address_space(3))) FusedLds FusedShared;
 static __device__ __forceinline__ uint32_t lds_at(const __attribute__((address_space(3))) void* p) {
   return (uint32_t)(uintptr_t)p;
+}
+
+// The kernel's arguments, read anew: what is taken from them here is not held in registers from one
+// use to the next (there are more than the scalar registers hold, and the compiler would keep them
+// in lanes of vector registers through the steps).
+static __device__ __forceinline__ const BwdArgs& fused_args() {
+  auto p = (const __attribute__((address_space(4))) BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const BwdArgs*)p;
 }
 
 // Per lane one of two arrays: x in lanes 0..31, y in the others.  (Both addresses are brought into
@@ -112,12 +134,13 @@ static __device__ __forceinline__ u32x2 lds_get_tr16(uint32_t addr) {
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)addr));
 }
 
-// dS byte offset of (key row, piece of four queries): rows of 64 bytes, 16-byte chunks and the
-// 8-byte halves in them moved about so that neither the writes (a lane per key) nor the transposing
-// reads (four keys by four pieces per 16 lanes) meet in a bank.
+// dS byte offset of (key row, piece of four queries): per 32 keys four runs of 512 bytes, of eight
+// queries each, key by key.  A wavefront's write fills a run; the transposing reads (four keys by four
+// pieces per 16 lanes) take two runs at a time, of which the second has its groups of eight keys
+// exchanged so that they do not meet in a bank.
 static __device__ __forceinline__ uint32_t ds_off(int row, int piece) {
-  const int f = ((row >> 1) & 2) | ((row >> 3) & 1);
-  return row * 64 + (((piece >> 1) ^ f) << 4) + (((piece & 1) ^ ((row >> 4) & 1)) << 3);
+  const int run = piece >> 1;
+  return (row >> 5) * 2048 + run * 512 + (((row & 31) ^ ((run & 1) << 3)) << 4) + ((piece & 1) << 3);
 }
 
 // Sum over 16 neighbouring lanes, the same in all of them: pairs, quads, halves, all.
@@ -179,8 +202,7 @@ struct FusedWave {
   uint32_t ds_wr;    // this lane's key's row of dS
   uint32_t stat_rd;  // LSE and D of the rows this lane's registers hold
   uint32_t sum_rd;   // this lane's four channels of dO and O of the row it helps to sum
-  uint32_t sum_row;  // that row's entry in the statistics
-  uint32_t sum_wr;   // where this lane's result goes
+  uint32_t sum_wr;   // where this lane's result goes; the lower 128: the row's entry in the statistics
   uint32_t carry_lane;  // this lane's place in a block of fp32 dQ
   uint32_t out_wr;      // in a block of dQ on its way out
   uint32_t out_lane;    // and in memory: of fp32 dQ, or of the rows that are read back whole
@@ -189,7 +211,6 @@ struct FusedWave {
   int64_t dq_step;   // bytes from block to block
   bool to_slab;      // not the last sweep
   float scale, c2;
-  GlobalFloat kept_at;  // (per lane)
 
   f32x16 dk[2], dv[2];       // dK^T, dV^T: column = key ln, rows = channels
   u32x4 kT[S::NCH][S::KS];   // K^T operands of the dQ products
@@ -209,13 +230,10 @@ struct FusedWave {
     stat_rd = 16 * g;
     const int row = kg * 4 * NH + g4;
     sum_rd = 2 * tile_off(row, 4 * c);
-    sum_row = 4 * row;
-    sum_wr = c < 2 ? 128 * c + 4 * row : 256 + 4 * (lane & 31);
+    sum_wr = 128 * min(c, 2) + 4 * row;
     to_slab = NH == 1 && ph.kt + 1 < ph.n_kt;
     scale = a.pb.scale;
     c2 = scale * kLog2e;
-    const int64_t first = uniform_i64((int64_t)ph.head * a.pb.total_tokens + ph.r0);
-    kept_at = per_half(a.lse2, a.dsum, first, lane) + (lane & 31);
     const uint16_t* dq0 = a.dq + uniform_i64((int64_t)(ph.r0 + 32 * ph.q0) * a.dq_stride + (ph.head + hd) * kHeadDim);
     carry_lane = (64 * wave + lane) * 16;
     if (to_slab) {
@@ -269,16 +287,16 @@ struct FusedWave {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // A operand of product i (0..7) of dV^T += dO^T P, dK^T += Q^T dS; `q` = Q of the block + col_rd
+  // A operand of product i (0..7) of dK^T += Q^T dS (first), dV^T += dO^T P; `q` = Q of the block + col_rd
   __device__ __forceinline__ u32x4 operand(uint32_t q, int i) const {
     constexpr uint32_t kToG = offsetof(FusedLds, g) - offsetof(FusedLds, q);
-    const uint32_t at = (q ^ ((i & 1) << 6)), off = ((i >> 1) & 1 ? 0 : kToG) + (i >> 2) * 2048;
+    const uint32_t at = (q ^ ((i & 1) << 6)), off = (i < 4 ? 0 : kToG) + ((i >> 1) & 1) * 2048;
     const u32x2 lo = lds_get_tr16(at + off), hi = lds_get_tr16((at ^ 32) + off + 1024);
     return u32x4{lo[0], lo[1], hi[0], hi[1]};
   }
   __device__ __forceinline__ void multiply(int i, u32x4 x) {
-    const int t2 = i >> 2, cb = i & 1;
-    if ((i >> 1) & 1)
+    const int t2 = (i >> 1) & 1, cb = i & 1;
+    if (i < 4)
       dk[cb] = Op<T>::mfma(x, ds[t2], dk[cb]);
     else
       dv[cb] = Op<T>::mfma(x, p[t2], dv[cb]);
@@ -286,8 +304,7 @@ struct FusedWave {
   // B operand of product i (0..7) of the dQ part; `d` = dS of the block + ds_rd
   __device__ __forceinline__ u32x4 dq_operand(uint32_t d, int i) const {
     const int h = (i / S::NCH) % S::NQH, k = i / (S::NCH * S::NQH);
-    const uint32_t at = d ^ (h << 5);
-    const u32x2 lo = lds_get_tr16(at + 2048 * k), hi = lds_get_tr16((at ^ 8) + 2048 * k + 1024);
+    const u32x2 lo = lds_get_tr16(d + 1024 * h + 2048 * k), hi = lds_get_tr16(d + 1024 * h + 2048 * k + 256);
     return u32x4{lo[0], lo[1], hi[0], hi[1]};
   }
   __device__ __forceinline__ void dq_multiply(int i, u32x4 x) {
@@ -303,7 +320,9 @@ struct FusedWave {
     const uint32_t q = lds_at(&lds.q[0][0]) + slot(j + S::D - 1) * 4096 + col_rd;
     const uint32_t d = ds_base(j - 1) + ds_rd, w = ds_base(j) + ds_wr;
     const uint32_t st = lds_at(&lds.stat[0][0]) + slot(j) * 512 + stat_rd;
-    u32x4 x[3], y[3];  // operands, fetched two groups ahead
+    // operands, fetched two groups ahead (DROP: one, whose groups are longer; two would not fit the registers)
+    constexpr int kAhead = DROP ? 1 : 2, kOps = kAhead + 1;
+    u32x4 x[kOps], y[kOps];
     f32x4 l4[2], d4[2];
     auto stats = [&](int i) {
       l4[i & 1] = lds_get<f32x4>(st + 32 * i);
@@ -311,52 +330,57 @@ struct FusedWave {
     };
     auto fetch = [&](int i) {
       if (FIRST) return;
-      x[i % 3] = operand(q, i);
-      y[i % 3] = dq_operand(d, i);
+      x[i % kOps] = operand(q, i);
+      y[i % kOps] = dq_operand(d, i);
     };
     fetch(0);
     stats(0);
-    fetch(1);
+    if (kAhead == 2) fetch(1);
     __builtin_amdgcn_sched_barrier(0);
-    u32x4 pn[2], dn[2];
+    // (dS of the block before is used up by the fourth product, P by the last: new ones are packed behind
+    // that, into the same registers)
+    float pe[16], de[4];
+    u32x4 pn[2];
 #pragma unroll
     for (int i = 0; i < 8; i++) {
       if (LATE && i == 2) __builtin_amdgcn_s_setprio(0);
       if (LATE && i == 7) __builtin_amdgcn_s_setprio(1);
-      if (i + 2 < 8) fetch(i + 2);
+      if (i + kAhead < 8) fetch(i + kAhead);
       if (i & 1 && i < 7) stats((i + 1) >> 1);
       if (!FIRST) {
-        multiply(i, x[i % 3]);
-        dq_multiply(i, y[i % 3]);
+        multiply(i, x[i % kOps]);
+        dq_multiply(i, y[i % kOps]);
       }
       const f32x4 l = l4[(i >> 1) & 1], dd = d4[(i >> 1) & 1];
       const float lv[2] = {l[2 * (i & 1)], l[2 * (i & 1) + 1]};
       const float dvv[2] = {dd[2 * (i & 1)], dd[2 * (i & 1) + 1]};
-      float pe[2], de[2];
 #pragma unroll
       for (int e = 0; e < 2; e++) {
         const int r = 2 * i + e;
         const float x0 = fast_exp2(__builtin_fmaf(s[r], c2, -lv[e]));
         if (DROP) {
           const bool on = kept(keep, r, a.drop.thr);
-          pe[e] = on ? x0 : 0.f;
-          de[e] = x0 * ((on ? dp[r] * a.drop.rp : 0.f) + dvv[e]);
+          pe[r] = on ? x0 : 0.f;
+          de[r & 3] = x0 * ((on ? dp[r] * a.drop.rp : 0.f) + dvv[e]);
         } else {
-          pe[e] = x0;
-          de[e] = x0 * dp[r];
+          pe[r] = x0;
+          de[r & 3] = x0 * dp[r];
         }
       }
-      pn[i >> 2][i & 3] = Op<T>::pack2(pe[0], pe[1]);
-      dn[i >> 2][i & 3] = Op<T>::pack2(de[0], de[1]);
-      if (i & 1)  // dS of this block for the dQ products of the next step
-        lds_put(w ^ ((i >> 1) << 4), u32x2{dn[i >> 2][(i & 3) - 1], dn[i >> 2][i & 3]});
+      if (DROP) {  // (chosen in fp32: the compiler would convert one by one and choose halves)
+        asm volatile("" : "+v"(pe[2 * i]), "+v"(pe[2 * i + 1]));
+        pn[i >> 2][i & 3] = Op<T>::pack2(pe[2 * i], pe[2 * i + 1]);
+      }
+      if (i & 1) {  // dS of this block, also for the dQ products of the next step
+        const u32x2 x = {Op<T>::pack2(de[0], de[1]), Op<T>::pack2(de[2], de[3])};
+        ds[i >> 2][(i & 3) - 1] = x[0];
+        ds[i >> 2][i & 3] = x[1];
+        lds_put((w ^ (((i >> 1) & 1) << 7)) + (i >> 1) * 512, x);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int t2 = 0; t2 < 2; t2++) {
-      p[t2] = pn[t2];
-      ds[t2] = dn[t2];
-    }
+    for (int i = 0; i < 8; i++) p[i >> 2][i & 3] = DROP ? pn[i >> 2][i & 3] : Op<T>::pack2(pe[2 * i], pe[2 * i + 1]);
   }
   // dV and dK of the last block
   __device__ __forceinline__ void last_products(int j) {
@@ -422,7 +446,7 @@ struct FusedWave {
   }
   // -D and LSE * log2(e) of block j, from its O, dO and LSE in the ring: 16 threads per row.
   __device__ __forceinline__ void statistics(int j) const {
-    const uint32_t u = slot(j);
+    const uint32_t u = slot(j), sum_row = sum_wr & 127;
     const uint32_t from = lds_at(&lds.g[0][0]) + u * 4096 + sum_rd, lse = lds_at(&lds.lse[0][0]) + u * 256 + sum_row;
     const uint32_t to = lds_at(&lds.stat[0][0]) + u * 512 + sum_wr;
     const int left = 4 * (ph.len - 32 * j);
@@ -436,18 +460,18 @@ struct FusedWave {
       const float d = sum16(Op<T>::dot2(gv[1], ov[1], Op<T>::dot2(gv[0], ov[0], 0.f)));
       const bool in = (int)sum_row + 16 * it < left;
       const float x = in ? l * kLog2e : INFINITY, y = in ? -d : 0.f;
-      lds_put(to + 16 * it, (lane_id() & 1) ? y : x);
+      lds_put(to + 16 * it, sum_wr < 128 ? x : y);
     }
   }
   // The statistics of block j stay in the workspace, for the sweeps that follow and as the two
-  // passes leave them; kept_at = this lane's place for block 0 of the first head (lanes 0..31 the LSE's,
-  // the others D's).
+  // passes leave them (lanes 0..31 the LSE's, the others D's).
   __device__ __forceinline__ void keep_statistics(int j) const {
     const int lane = lane_id(), row = lane & 31;
+    const BwdArgs& b = fused_args();
 #pragma unroll
     for (int h = 0; h < NH; h++)
-      if ((NH == 1 || ph.head + h < a.pb.heads) && 32 * j + row < ph.len)
-        kept_at[(int64_t)h * a.pb.total_tokens + 32 * j] =
+      if ((NH == 1 || ph.head + h < b.pb.heads) && 32 * j + row < ph.len)
+        per_half(b.lse2, b.dsum, uniform_i64((int64_t)(ph.head + h) * b.pb.total_tokens + ph.r0 + 32 * j), lane)[row] =
             lds_get<float>(lds_at(&lds.stat[0][0]) + ((j & (S::D - 1)) * NH + h) * 512 + 4 * lane);
   }
   // dK and dV of this wavefront's keys (zeros where a key is masked), and zeros for the keys behind
@@ -638,6 +662,12 @@ static __device__ __forceinline__ void fused_begin(const BwdArgs& a, const Fused
     wave < 4 ? two(std::true_type{}, std::integral_constant<bool, NH == 1>{}) : two(std::false_type{}, std::integral_constant<bool, NH == 1>{});
 }
 
+// A sweep of at least so many blocks finds the next item's sequence in LDS before its last products: it is
+// requested after the first step, and has landed when the step so many less one opens.  (NH == 1: the
+// four groups of transfers that follow it leave three under way then.)
+template <int NH>
+constexpr int kFusedNext = NH == 1 ? 4 : NH == 2 ? 3 : 2;
+
 // The steps of a sweep, for wavefronts 0..3 (LATE = false) and 4..7.  The former form the scores of
 // block j + 1 at the end of step j, the latter those of block j at its start: the two of a SIMD then
 // have their products and their exponentials at different times.  Of two wavefronts of one priority the
@@ -681,6 +711,7 @@ static __device__ __forceinline__ void fused_steps(FusedWave<T, NH, DROP>& fw, c
   auto open = [&](int j) {
     if (NH > 1) {
       if (j == q0) wait_vmem<0>();  // (the ring holds all there is)
+      if (!LATE && wave == 0 && j == q0 + kFusedNext<NH> - 1) wait_vmem<0>();  // (the next item's sequence)
     } else if (j > q0 + 2) {
       if (AGAIN && carry_in)
         wait_vmem<3 * (Pull::kGroup + 1)>();
@@ -749,18 +780,9 @@ static __device__ __forceinline__ void fused_steps(FusedWave<T, NH, DROP>& fw, c
   }
 }
 
-// The kernel's arguments, read anew: what is taken from them here is not held in registers from one
-// use to the next (there are more than the scalar registers hold, and the compiler would keep them
-// in lanes of vector registers through the steps).
-static __device__ __forceinline__ const BwdArgs& fused_args() {
-  auto p = (const __attribute__((address_space(4))) BwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return *(const BwdArgs*)p;
-}
-
 // A sweep from "its first transfers have landed" to its results and to the first transfers of the one
-// after it.  `publish` is called once in it, at least a barrier ahead of `next`, which finds out
-// whether there is another sweep and puts it into nx.  Returns that.
+// after it.  `publish` is called once in it, behind its first step; `next` then finds out whether
+// there is another sweep and puts it into nx.  Returns that.
 template <typename T, int NH, bool DROP, typename Publish, typename Next>
 static __device__ __forceinline__ bool fused_sweep(const FusedPhase& phase, const FusedPhase& nx, FusedShared& lds, int wave, u32x4* slab,
                                                    u32x4 (&kb)[4], u32x4 (&vb)[4], Publish publish, Next next) {
@@ -829,8 +851,8 @@ static __device__ __forceinline__ bool fused_sweep(const FusedPhase& phase, cons
   const bool want_dq = ph.want & 2, rows_out = want_dq && !fw.to_slab && (NH == 2 || wave >= 4);
   // The next sweep's K and V are requested now (their registers are free), its first query blocks
   // behind the barrier.
-  const bool one = q1 - q0 == 1;  // (then what was published is only seen behind the barrier)
-  bool more = !one && next();
+  const bool few = q1 - q0 < kFusedNext<NH>;  // (then what was published is only seen behind the barrier)
+  bool more = !few && next();
   if (more) fused_load_kv<NH>(fused_args(), nx.scalar(), wave, kb, vb);
   if (wave_on) fw.last_products(q1 - 1);
   if (more)
@@ -840,12 +862,11 @@ static __device__ __forceinline__ bool fused_sweep(const FusedPhase& phase, cons
   // (read ahead of the barrier: the next sweep's transfers may go to the same place)
   if (want_dq) fw.dq_begin(((q1 - 1 - q0) & (kCarry - 1)) * (kFusedThreads * 16), again && ph.kt > 0);
   lds_barrier();
-  if (one) {
+  if (few) {
     more = next();
     if (more) fused_load_kv<NH>(fused_args(), nx.scalar(), wave, kb, vb);
-  } else if (rows_out) {
-    fw.dq_out(q1 - 2);
   }
+  if (rows_out && q1 - q0 > 1) fw.dq_out(q1 - 2);
   if (more) fused_begin<NH>(fused_args(), nx, lds, wave);
   if (want_dq) {
     fw.dq_products(q1 - 1);
@@ -854,13 +875,16 @@ static __device__ __forceinline__ bool fused_sweep(const FusedPhase& phase, cons
     fw.dq_finish(q1 - 1, NH != 2);
   }
   if (NH > 1) lds_barrier();
-  // The next sweep's K, V and first blocks are awaited here, ahead of the stores that follow: later
-  // a wait would be for those as well.
-  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  if (NH == 2 && rows_out) fw.dq_out(q1 - 1);
+  // The next sweep's K, V and first blocks have to have landed at the end.  Behind them there are at
+  // least the 8 stores of a whole tile of keys, which need not be awaited.
+  if (ph.want & 1) fw.store_keys(fused_args());
+  if ((ph.want & 1) && key0 + 32 * fw.kg + 32 <= ph.len && ph.head + fw.hd < a.pb.heads)
+    wait_vmem<8>();
+  else
+    wait_vmem<0>();
 #pragma unroll
   for (int t = 0; t < 4; t++) asm volatile("" : "+v"(kb[t]), "+v"(vb[t]));
-  if (NH == 2 && rows_out) fw.dq_out(q1 - 1);
-  if (ph.want & 1) fw.store_keys(fused_args());
   return more;
 }
 
@@ -890,22 +914,21 @@ static __device__ __forceinline__ int fused_items(const BwdArgs& a, FusedShared&
       }
     }
   };
-  auto phase_of = [&](int i) {
+  auto phase_of = [&](int i, int rec, int r0, int len, int nk) {
     FusedPhase ph;
-    const BwdArgs& a = fused_args();
-    const int rec = (i - begin) / groups;
     ph.head = NH * (i - begin - rec * groups);
-    ConstInt p = (ConstInt)(uintptr_t)(a.seqs + record + rec);
-    ph.r0 = p[0];
-    ph.len = p[1];
-    ph.nk = p[2];
+    ph.r0 = r0;
+    ph.len = len;
+    ph.nk = nk;
     ph.n_kt = NH > 1 ? 1 : max((ph.nk + kFusedKeys - 1) / kFusedKeys, 1);
     const int nq = (ph.len + 31) >> 5;
     ph.steps = ph.n_kt == 1 || nq <= fit ? ph.n_kt : ph.n_kt * (1 + (nq + fit - 1) / fit);
     set_step(ph, 0);
-    return ph;
+    return ph.scalar();
   };
-  FusedPhase ph = phase_of(item);
+  const int rec0 = (item - begin) / groups;
+  ConstInt p = (ConstInt)(uintptr_t)(a.seqs + record + rec0);
+  FusedPhase ph = phase_of(item, rec0, p[0], p[1], p[2]);
   u32x4 kb[4], vb[4];
   fused_load_kv<NH>(a, ph, wave, kb, vb);
   fused_begin<NH>(a, ph, lds, wave);
@@ -913,21 +936,31 @@ static __device__ __forceinline__ int fused_items(const BwdArgs& a, FusedShared&
 #pragma unroll
   for (int t = 0; t < 4; t++) asm volatile("" : "+v"(kb[t]), "+v"(vb[t]));
   while (true) {
-    const bool last = ph.step + 1 == ph.steps;
+    const bool last = NH > 1 || ph.step + 1 == ph.steps;
     uint32_t claimed = 0;
     if (last && threadIdx.x == 0)
       claimed = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     FusedPhase nx = ph;
     auto publish = [&]() {
-      if (last && threadIdx.x == 0) lds.mailbox = claimed;
+      if (!last || wave != 0) return;
+      const int it = (per_class + __builtin_amdgcn_readfirstlane((int)claimed)) * kFeedClasses + cls;
+      const int rec = (it - begin) / groups;
+      if (lane_id() == 0) {
+        lds.mail[0] = it;
+        lds.mail[1] = rec;
+        if (it < end) dma16s((const void*)(uintptr_t)uniform_i64((int64_t)(uintptr_t)(fused_args().seqs + record + rec)), 0, lds_at(&lds.record));
+      }
     };
     auto next = [&]() {
-      if (last) {
-        item = (per_class + __builtin_amdgcn_readfirstlane((int)lds.mailbox)) * kFeedClasses + cls;
+      if (NH > 1 || last) {
+        auto s = [](uint32_t x) { return __builtin_amdgcn_readfirstlane((int)x); };
+        item = s(lds.mail[0]);
         if (item >= end) return false;
-        nx = phase_of(item);
+        const u32x4 r = lds_get<u32x4>(lds_at(&lds.record));
+        nx = phase_of(item, s(lds.mail[1]), s(r[0]), s(r[1]), s(r[2]));
       } else {
         set_step(nx, ph.step + 1);
+        nx = nx.scalar();
       }
       return true;
     };

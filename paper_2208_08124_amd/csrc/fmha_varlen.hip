@@ -56,8 +56,11 @@ struct Workspace {
   size_t count_off, feed_off, list_off, seqs_off, dsum_off, lse2_off, slab_off, bytes_list, bytes_fwd, bytes_bwd;
 };
 
-// Workgroups of the one-pass backward, and rows of fp32 dQ that each may be given.
+// Workgroups of the one-pass backward at most, and rows of fp32 dQ that each may be given.
 constexpr int64_t kFusedGrid = 256, kFusedSlabRows = 2048;
+
+// Workgroups of the one-pass backward: one per compute unit, a multiple of 8.
+int64_t fused_grid(int64_t items) { return ((items < kFusedGrid ? items : kFusedGrid) + 7) / 8 * 8; }
 
 Workspace carve(void* base, int64_t batch, int64_t total_tokens, int64_t heads) {
   Workspace w;
@@ -73,11 +76,13 @@ Workspace carve(void* base, int64_t batch, int64_t total_tokens, int64_t heads) 
   const size_t stat_bytes = round_up(sizeof(float) * ((size_t)total_tokens * (size_t)heads + 1), kAlign);
   w.lse2_off = w.dsum_off + stat_bytes;
   // dQ between sweeps: a workgroup needs no more rows than a sequence has, and there are no more
-  // workgroups on long sequences than there are rows in all heads
+  // workgroups on long sequences than there are rows in all heads; but 256 rows for every workgroup
+  // in any case (what is stated of the longest sequence may be wrong)
   w.slab_off = w.lse2_off + stat_bytes;
   const int64_t rows = ((int64_t)total_tokens + 255) / 256 * 256;
   int64_t slab = kFusedGrid * (rows < kFusedSlabRows ? rows : kFusedSlabRows);
   if (slab > rows * heads) slab = rows * heads;
+  if (slab < fused_grid(batch * heads) * fmha::kFusedKeys) slab = fused_grid(batch * heads) * fmha::kFusedKeys;
   if (total_tokens <= fmha::kFusedKeys) slab = 0;
   w.bytes_bwd = w.slab_off + (size_t)slab * fmha::kHeadDim * sizeof(float);
   // (base is null when only the sizes are wanted: no pointer arithmetic on it then)
@@ -220,12 +225,6 @@ unsigned feed_grid(const fmha_varlen_params_t* p, int per_cu, const Workspace& w
   return (unsigned)g;
 }
 
-// Workgroups of the one-pass backward: one per compute unit, a multiple of 8.
-int64_t fused_grid(const fmha_varlen_params_t* p) {
-  const int64_t items = (int64_t)p->batch * p->heads;
-  return ((items < kFusedGrid ? items : kFusedGrid) + 7) / 8 * 8;
-}
-
 // Rows of fp32 dQ for each workgroup of the one-pass backward.
 // (a multiple of 256: the sweeps of a sequence that needs more begin at multiples of eight blocks)
 int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
@@ -234,23 +233,44 @@ int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
   return (int32_t)(rows < kFusedSlabRows ? rows : kFusedSlabRows);
 }
 
-// Whether the backward runs as one pass (bwd_fused_kernel.h) or as two (bwd_kernels.h).  The one
-// pass is 1.1 - 1.4 times as fast while all compute units are busy, but its items are whole sequences: it
-// is taken where the longest one is at most 1 / 0.6 of a compute unit's share of the work, estimated from
-// below by what the batch would be with all sequences as long (then it is rarely a third longer than
-// its share; two passes have tiles of 128 rows to deal out).  Sequences of up to 64 (128) tokens are
-// taken four (two) heads at a time; with head counts that leave a quarter (fifth) of those places empty the
-// gain there is gone (1097 sequences of up to 109, 2 heads, dropout: 100 us in two passes, 112 in one).
-bool one_pass(const fmha_varlen_params_t* p, const Workspace& w) {
+// Whether the backward runs as one pass (bwd_fused_kernel.h) or as two (bwd_kernels.h).  The figures are
+// two passes' time over one's, 16 heads unless stated, without / with dropout.
+//
+// The one pass is 1.15 - 1.5 / 1.1 - 1.8 times as fast while all compute units are busy, but its items are
+// whole sequences, where the two passes have tiles of 128 rows to deal out.  A compute unit's share of the
+// work is estimated from below by what the batch would be with all sequences as long.
+//  - Up to 256 tokens (one sweep an item) it pays from a fifth of the longest sequence on: 0.98 / 0.99 at
+//    0.12 - 0.15, 1.04 - 1.14 / 1.06 - 1.19 at 0.2 - 0.5, even where a second round of items is nearly empty
+//    (272 equal items of 256 tokens: 1.07 / 1.17).
+//  - Longer sequences of mixed lengths: 0.99 / 1.00 at 0.39 of the longest, 1.06 - 1.11 / 1.12 - 1.14 at 0.61 - 0.64.
+//  - Longer ones that are (nearly) all equal take whole rounds: 0.83 - 0.91 / 0.82 - 0.87 where the rounds are
+//    0.56 - 0.69 full (0.95 / 0.85 for 160 items of 1024, but 1.10 / 1.18 for 160 of 512), 1.05 / 1.04 at 0.75.
+//    With few keys in a second sweep dropout costs more there than it saves: 272 ... 384 tokens 1.01 - 1.08 /
+//    0.94 - 0.97.
+// Sequences of up to 64 (128) tokens are taken four (two) heads at a time, and places without a head cost as
+// much as others.  Heads 1 / 2 / 3 / 5 / 6, without dropout: up to 64 tokens 0.47 / 0.87 / 1.09 / 0.89 / 1.02, up to 128
+// 0.6 / 0.96 / 0.92 / 0.95 / 1.0, up to 160 0.79 / 1.12 / 0.97, up to 256 1.0 / 1.17 / 0.94; with dropout (where an
+// empty place makes no mask) 0.6 / 1.1 / 1.4 / 1.16 / 1.34, 0.67 / 1.12 / 1.07 / 1.12 / 1.19, 0.92 / 1.21 / 1.07, 1.07 / 1.2 / 1.0.
+bool one_pass(const fmha_varlen_params_t* p, const Workspace& w, bool dropout) {
   if (p->flags & (FMHA_FLAG_BWD_ONLY_DQ | FMHA_FLAG_BWD_ONLY_DKV)) return false;
-  if (p->max_seqlen <= 0) return false;
-  const int h = p->heads;
-  if (p->max_seqlen <= 128 && (h < 0.8 * ((h + 1) / 2 * 2) || h < 0.75 * ((h + 3) / 4 * 4))) return false;
-  const size_t slab = (size_t)fused_grid(p) * (size_t)fused_slab_rows(p) * fmha::kHeadDim * sizeof(float);
-  if (p->max_seqlen > fmha::kFusedKeys && w.bytes_bwd - w.slab_off < slab) return false;
+  const int n = p->max_seqlen, h = p->heads;
+  if (n <= 0) return false;
+  if (dropout) {
+    if (h == 1 && n <= 192) return false;
+  } else {
+    if (n <= 128 && h < 0.75 * ((h + 3) / 4 * 4)) return false;
+    if (n > 64 && n <= fmha::kFusedKeys && h < 0.8 * ((h + 1) / 2 * 2)) return false;
+  }
+  const size_t slab = (size_t)fused_grid((int64_t)p->batch * p->heads) * (size_t)fused_slab_rows(p) * fmha::kHeadDim * sizeof(float);
+  if (p->total_tokens > fmha::kFusedKeys && w.bytes_bwd - w.slab_off < slab) return false;
   // in steps of 256 keys by 32 queries
-  const double longest = (double)((p->max_seqlen + 255) / 256) * ((p->max_seqlen + 31) / 32);
+  const double longest = (double)((n + 255) / 256) * ((n + 31) / 32);
   const double share = (double)p->total_tokens * p->total_tokens * h / ((double)p->batch * 256 * 32 * kFusedGrid);
+  if (n <= fmha::kFusedKeys) return share >= 0.2 * longest;
+  if (p->total_tokens >= 0.9 * n * p->batch) {
+    const int64_t items = (int64_t)p->batch * h, rounds = (items + kFusedGrid - 1) / kFusedGrid;
+    return items >= 0.7 * (double)(rounds * kFusedGrid) && !(dropout && n <= 416);
+  }
   return share >= 0.6 * longest;
 }
 
@@ -504,8 +524,8 @@ int run_bwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   a.dq = static_cast<uint16_t*>(dq);
   a.dk = static_cast<uint16_t*>(dk);
   a.dv = static_cast<uint16_t*>(dv);
-  if (one_pass(p, w)) {
-    const int64_t grid = fused_grid(p);
+  if (one_pass(p, w, da.thr != 0)) {
+    const int64_t grid = fused_grid((int64_t)p->batch * p->heads);
     a.seqs = w.seqs;
     a.slab = w.slab;
     a.slab_rows = fused_slab_rows(p);
