@@ -242,7 +242,10 @@ int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
 //  - Up to 256 tokens (one sweep an item) it pays from a fifth of the longest sequence on: 0.98 / 0.99 at
 //    0.12 - 0.15, 1.04 - 1.14 / 1.06 - 1.19 at 0.2 - 0.5, even where a second round of items is nearly empty
 //    (272 equal items of 256 tokens: 1.07 / 1.17).
-//  - Longer sequences of mixed lengths: 0.99 / 1.00 at 0.39 of the longest, 1.06 - 1.11 / 1.12 - 1.14 at 0.61 - 0.64.
+//  - Longer sequences of mixed lengths: 0.98 - 1.01 / 0.95 - 1.02 at 0.36 - 0.48 of the longest, 1.06 - 1.16 / 1.12 - 1.17 at
+//    0.58 - 0.64 (one batch of 34, up to 1024 tokens, 0.81 / 1.02 at 0.67); above 1024 tokens, where there is less to be gained,
+//    0.95 - 0.98 / 0.86 - 0.90 at 0.60 - 0.64.  Where most are short the squares of the longer ones make the share
+//    larger than it is estimated here: 1.07 - 1.17 / 1.17 - 1.25 from 0.24 on (lengths of a fifth of the longest on average).
 //  - Longer ones that are (nearly) all equal take whole rounds: 0.83 - 0.91 / 0.82 - 0.87 where the rounds are
 //    0.56 - 0.69 full (0.95 / 0.85 for 160 items of 1024, but 1.10 / 1.18 for 160 of 512), 1.05 / 1.04 at 0.75.
 //    With few keys in a second sweep dropout costs more there than it saves: 272 ... 384 tokens 1.01 - 1.08 /
@@ -271,7 +274,8 @@ bool one_pass(const fmha_varlen_params_t* p, const Workspace& w, bool dropout) {
     const int64_t items = (int64_t)p->batch * h, rounds = (items + kFusedGrid - 1) / kFusedGrid;
     return items >= 0.7 * (double)(rounds * kFusedGrid) && !(dropout && n <= 416);
   }
-  return share >= 0.6 * longest;
+  if (n > 1024) return share >= 0.9 * longest;
+  return share >= (p->total_tokens < 0.3 * n * p->batch ? 0.3 : 0.6) * longest;
 }
 
 // Dropout arguments for the kernels; d == nullptr means no dropout.
