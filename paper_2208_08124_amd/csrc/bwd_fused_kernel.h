@@ -553,15 +553,16 @@ struct FusedPull {
     } else {
       part(0, a.d_o, a.do_stride, row0, head, &lds.g[0][0], wave);
     }
-    if (!kTail) return;
-    const int l = lane_id();
-    if (AGAIN) {
-      stat = per_half(a.lse2, a.dsum, uniform_i64((int64_t)head * a.pb.total_tokens + row0), l) + (l & 31);
-      tail_to = __builtin_amdgcn_readfirstlane(lds_at(&lds.stat[0][0]));
-    } else {
-      tail = scalar(a.lse + (int64_t)head * a.pb.total_tokens + row0);
-      tail_lane = 4u * (l & 31);
-      tail_to = __builtin_amdgcn_readfirstlane(lds_at(&lds.lse[hd][0]));
+    if (kTail) {
+      const int l = lane_id();
+      if (AGAIN) {
+        stat = per_half(a.lse2, a.dsum, uniform_i64((int64_t)head * a.pb.total_tokens + row0), l) + (l & 31);
+        tail_to = __builtin_amdgcn_readfirstlane(lds_at(&lds.stat[0][0]));
+      } else {
+        tail = scalar(a.lse + (int64_t)head * a.pb.total_tokens + row0);
+        tail_lane = 4u * (l & 31);
+        tail_to = __builtin_amdgcn_readfirstlane(lds_at(&lds.lse[hd][0]));
+      }
     }
     if (left < 32) last(a, wave);
   }
