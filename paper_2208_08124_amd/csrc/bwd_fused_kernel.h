@@ -160,8 +160,12 @@ static __device__ __forceinline__ void lds_barrier() {
 }
 
 // 4 bytes per lane, wave-uniform base and byte offset per lane (see dma16s)
-static __device__ __forceinline__ void dma4s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_byte_addr), "v"(voff), "s"(sbase) : "memory");
+static __device__ __forceinline__ void dma4s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr, uint32_t more) {
+  const void* base;
+  asm volatile("s_add_u32 m0, %1, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
+               : "=&s"(base)
+               : "s"(lds_byte_addr), "v"(voff), "s"(sbase), "s"(more)
+               : "memory", "scc");
 }
 
 // 4 KB of LDS for wavefront (or group of keys) w between two sweeps.  NH == 1: the ring's last four places,
@@ -585,18 +589,18 @@ struct FusedPull {
     const uint32_t place = (j & (D - 1)) * NH;
 #pragma unroll
     for (int i = 0; i < kParts; i++) {
-      dma16s(src[i], lane[i], to[i] + 4096u * place);
+      dma16s(src[i], lane[i], to[i], 4096u * place);
       if (NH == 4) {  // sixteen rows on
         const int r = 8 * piece(wave) + (lane_id() >> 3);
         const int more = min(16, max(left - 1 - r, 0));
-        dma16s(src[i], lane[i] + (uint32_t)more * (uint32_t)(step[i] >> 5), to[i] + 4096u * place + 2048u);
+        dma16s(src[i], lane[i] + (uint32_t)more * (uint32_t)(step[i] >> 5), to[i], 4096u * place + 2048u);
       }
     }
     if (kTail) {
       if (AGAIN)
         dma4((const float*)stat, tail_to + 512u * place);
       else
-        dma4s(tail, tail_lane, tail_to + 256u * place);
+        dma4s(tail, tail_lane, tail_to, 256u * place);
     }
     if (left > 32) {
 #pragma unroll
@@ -691,7 +695,7 @@ static __device__ __forceinline__ void fused_steps(FusedWave<T, NH, DROP>& fw, c
   uint32_t place = 0;
   int carry_left = q1 - q0;
   auto carry_fetch = [&]() {
-    dma16s(carry_src, fw.carry_lane, carry_to + place);
+    dma16s(carry_src, fw.carry_lane, carry_to, place);
     if (--carry_left > 0) carry_src += kFusedThreads * 16;
     place = (place + kFusedThreads * 16) & (kCarry * kFusedThreads * 16 - 1);
   };

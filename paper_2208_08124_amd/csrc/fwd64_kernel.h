@@ -72,9 +72,14 @@ struct DmaLane32 {
 // 32 full rows starting at `rows` (wave-uniform); lane_bytes = (row * stride + chunk * 8) * 2.
 static __device__ __forceinline__ void dma_tile32_full(const uint16_t* rows, uint32_t lane_bytes, int64_t stride,
                                                        int wave, uint32_t tile_addr) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane(tile_addr + 1024u * wave);
-  dma16s(rows, lane_bytes, m0);
-  dma16s(rows + 16 * stride, lane_bytes, m0 + 2048u);
+  // Both under one m0, since an instruction's offset counts for the LDS address and for the other one.  The bases
+  // come out of scalar additions, so that they need no copies (a test of the built instructions watches that).
+  const uint16_t* second = rows + (16 * stride - 1024);
+  asm volatile(
+      "s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\tglobal_load_lds_dwordx4 %2, %4 offset:2048"
+      :
+      : "s"(tile_addr), "s"(1024u * wave), "v"(lane_bytes), "s"(rows), "s"(second)
+      : "memory", "scc");
 }
 
 // Rows [row0, row0 + 32) clamped to last_row (the tail of a sequence repeats its last row).

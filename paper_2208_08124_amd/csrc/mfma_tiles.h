@@ -188,33 +188,44 @@ struct ColRead {
 // it in clobber lists with a warning) - the compiler never keeps a value of its own in m0
 // across other instructions, it writes m0 directly ahead of each instruction of its own
 // that reads it.
+// The waits that the instruction set asks for between a write and the transfer that reads it
+// are the statement's own affair, since the compiler places none inside it: one wait state after m0,
+// five after a vector instruction that wrote the base's scalar registers (v_readlane,
+// v_readfirstlane; the compiler may put one directly ahead of the statement, for instance to fetch
+// a base that it keeps in a lane of a vector register).  A base read too early is an address
+// that nobody formed.  Scalar instructions do wait for what vector instructions write, and nothing has to be
+// waited for after them: so the base is copied by one, which also stands between m0 and the transfer.  A forward
+// call on nine sequences takes 11.17 us without these waits, 11.5 with the five states spent idle (s_nop 3), 11.3
+// with copies everywhere and 11.23 with the pairs of fwd64_kernel.h, which need one wait for two transfers.
 // ---------------------------------------------------------------------------
 static __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
-static __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds_byte_addr), "v"(gptr)
-               : "memory");
-}
-
-// Same for 4 bytes per lane: the wavefront's 64 dwords land at m0 + 4*lane.
+// 4 bytes per lane: the wavefront's 64 dwords land at m0 + 4*lane.
 static __device__ __forceinline__ void dma4(const void* gptr, uint32_t lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
                :
                : "s"(lds_byte_addr), "v"(gptr)
                : "memory");
 }
 
-// The same with the address split into a wave-uniform base (scalar registers) and a
-// 32-bit byte offset per lane: no 64-bit vector arithmetic per transfer.
+// 16 bytes per lane, the address split into a wave-uniform base (scalar registers) and a
+// 32-bit byte offset per lane: no 64-bit vector arithmetic per transfer.  (The second form adds
+// up the LDS address itself.)
 static __device__ __forceinline__ void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
+  const void* base;
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+               : "=&s"(base)
                : "s"(lds_byte_addr), "v"(voff), "s"(sbase)
                : "memory");
+}
+static __device__ __forceinline__ void dma16s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr, uint32_t more) {
+  const void* base;
+  asm volatile("s_add_u32 m0, %1, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+               : "=&s"(base)
+               : "s"(lds_byte_addr), "v"(voff), "s"(sbase), "s"(more)
+               : "memory", "scc");
 }
 
 // An offset the compiler may keep in scalar registers: the value is the same in every lane
@@ -250,7 +261,7 @@ static __device__ __forceinline__ void dma_tile_full(const uint16_t* rows, uint3
                                                      int wave, uint32_t tile_addr) {
   const uint32_t m0 = __builtin_amdgcn_readfirstlane(tile_addr + 1024u * wave);
   dma16s(rows, lane_bytes, m0);
-  dma16s(rows + 32 * stride, lane_bytes, m0 + 4096u);
+  dma16s(rows + 32 * stride, lane_bytes, m0, 4096u);
 }
 
 // Start moving rows [row0, row0 + 64) of a packed tensor (rows clamped to
@@ -265,7 +276,7 @@ static __device__ __forceinline__ void dma_tile(const uint16_t* base, int64_t st
   const uint16_t* rows = base + uniform_i64(row0 * stride);
   const uint32_t st = (uint32_t)stride;
   dma16s(rows, (ra * st + dl.chunk * 8) * 2u, m0);
-  dma16s(rows, (rb * st + dl.chunk * 8) * 2u, m0 + 4096u);
+  dma16s(rows, (rb * st + dl.chunk * 8) * 2u, m0, 4096u);
 }
 
 // ---------------------------------------------------------------------------
@@ -302,12 +313,13 @@ __device__ __forceinline__ void rotate_priority(int step, int slot, int slots) {
 
 // Lane number, recomputed from the execution mask (all 64 lanes active): two
 // instructions where it is needed beat a register - and everything the compiler
-// would derive from it ahead of time - held through the hot loop.  Volatile, so
-// that it stays where it is written.
+// would derive from it ahead of time - held through the hot loop.  The empty statement is
+// volatile, so that they stay where they are written; the instructions themselves are the compiler's,
+// which knows how long a matrix instruction still reads the register that they go to.
 __device__ __forceinline__ int lane_id() {
-  int x;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
-  return x;
+  uint32_t zero = 0;
+  asm volatile("" : "+s"(zero));
+  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
 }
 
 // A wavefront's 32 x 64 result tile, held transposed in MFMA layout (x[cb][r] =

@@ -109,8 +109,8 @@ inline uint32_t fetch_add(uint32_t* p, uint32_t v) {
 #define __builtin_amdgcn_sched_barrier(x)
 #define __builtin_amdgcn_s_setprio(x)
 #define __builtin_amdgcn_exp2f(x) exp2f(x)
-#define __builtin_amdgcn_mbcnt_lo(mask, x) (x)
-#define __builtin_amdgcn_mbcnt_hi(mask, x) (emu::thread().x & 63)
+#define __builtin_amdgcn_mbcnt_lo(mask, below) (below)
+#define __builtin_amdgcn_mbcnt_hi(mask, below) (emu::thread().x & 63)
 #define __builtin_amdgcn_alignbit(hi, lo, s) emu::align_bits(hi, lo, s)
 #define __builtin_amdgcn_perm(hi, lo, s) emu::permute(hi, lo, s)
 #define __builtin_amdgcn_bitop3_b32(a, b, c, table) ((a) ^ (b) ^ (c))

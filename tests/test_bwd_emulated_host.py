@@ -24,11 +24,10 @@ def statement(m):
     s = m.group(0)
     if "load_lds" in s:
         size = 16 if "dwordx4" in s else 4
-        return f"emu::dma({'(const char*)sbase + voff' if 'sbase' in s else 'gptr'}, lds_byte_addr, {size});"
+        to = "lds_byte_addr + more" if "(more)" in s else "lds_byte_addr"
+        return f"emu::dma({'(const char*)sbase + voff' if 'sbase' in s else 'gptr'}, {to}, {size});"
     if "s_barrier" in s:
         return "emu::meet(emu::kWorkgroup);"
-    if "v_mbcnt" in s:
-        return "x = emu::thread().x & 63;"
     return ";"  # waits, and values held in registers
 
 
