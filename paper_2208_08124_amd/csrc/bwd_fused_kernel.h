@@ -60,7 +60,7 @@ struct FusedLds {
   uint16_t ds[2][kFusedKeys * 32];   // dS of a block: [key][query]; K tiles at the start, rows on their way out at the end
   uint16_t rows[2][2][32 * 64];      // finished dQ of a block (of two heads), on its way out
   float lse[kFusedSlots][64];
-  float stat[kFusedSlots][128];      // LSE * log2(e) of 32 rows, -D of 32 rows; the other half takes what lanes without a row write
+  float stat[kFusedSlots][128];      // LSE * log2(e) of 32 rows, -D of 32 rows; then +inf and 0, for keys that do not exist
   u32x4 record;   // the next item's sequence
   int mail[2];    // the next item, and its sequence's place among those of the section
 };
@@ -204,9 +204,9 @@ struct FusedWave {
   uint32_t col_rd;   // the same transposed
   uint32_t ds_rd;    // dS for the dQ products (query half 0 of them, or this wavefront's)
   uint32_t ds_wr;    // this lane's key's row of dS
-  uint32_t stat_rd;  // LSE and D of the rows this lane's registers hold
+  uint32_t stat_rd;  // LSE and D of the rows this lane's registers hold; what stands for them if its key does not exist
   uint32_t sum_rd;   // this lane's four channels of dO and O of the row it helps to sum
-  uint32_t sum_wr;   // where this lane's result goes; the lower 128: the row's entry in the statistics
+  uint32_t sum_wr;   // where this lane's result goes (one lane in sixteen the LSE, the others D); the lower 128: the row's entry
   uint32_t carry_lane;  // this lane's place in a block of fp32 dQ
   uint32_t out_wr;      // in a block of dQ on its way out
   uint32_t out_lane;    // and in memory: of fp32 dQ, or of the rows that are read back whole
@@ -231,10 +231,13 @@ struct FusedWave {
     col_rd = 2 * tile_off(4 * g + e, 16 * (g4 & 1) + 4 * pc);
     ds_rd = ds_off(4 * g4 + e, (NH == 1 ? 4 * (wave & 1) : 0) + pc) + hd * (S::KG * 2048);
     ds_wr = ds_off(32 * wave + ln, g);
-    stat_rd = 16 * g;
+    // A key place without a key holds a copy of the last key, and draws a mask of its own: its dS belongs to no score, and
+    // one that overflows the 16-bit type would be inf * 0 in the dQ products.  Its probabilities are zeros, by the LSE
+    // that it reads (any of 32; not from the banks that its neighbours read); V is cleared in fused_sweep.
+    stat_rd = ph.kt * kFusedKeys + 32 * kg + ln < ph.nk ? 16 * g : 272 - 16 * g;
     const int row = kg * 4 * NH + g4;
     sum_rd = 2 * tile_off(row, 4 * c);
-    sum_wr = 128 * min(c, 2) + 4 * row;
+    sum_wr = 128 * min(c, 1) + 4 * row;
     to_slab = NH == 1 && ph.kt + 1 < ph.n_kt;
     scale = a.pb.scale;
     c2 = scale * kLog2e;
@@ -803,6 +806,11 @@ static __device__ __forceinline__ bool fused_sweep(const FusedPhase& phase, cons
     fused_operands(tile, fw.row_rd, vb);
     fused_operands(tile, fw.row_rd, kb);  // (read back transposed by all wavefronts below)
   }
+  if (key0 + 32 * fw.kg + 32 > ph.nk) {  // (dP of a key that does not exist is 0, whatever its copy of V gives)
+    const uint32_t on = key0 + 32 * fw.kg + (lane_id() & 31) < ph.nk ? 0xffffffffu : 0u;
+#pragma unroll
+    for (int t = 0; t < 4; t++) vb[t] &= u32x4{on, on, on, on};
+  }
   lds_barrier();
   {
     const int lane = lane_id();
@@ -996,6 +1004,8 @@ __global__ __launch_bounds__(kFusedThreads, 2) void bwd_fused_kernel(const BwdAr
   const int cls = blockIdx.x & 7, per_class = gridDim.x >> 3;
   int item = (int)(blockIdx.x >> 3) * kFeedClasses + cls;
   FusedShared& shared = *(FusedShared*)&lds;
+  static_assert(kFusedThreads == 64 * kFusedSlots, "one thread per entry");
+  lds.stat[threadIdx.x >> 6][64 + (threadIdx.x & 63)] = (threadIdx.x & 32) ? 0.f : INFINITY;
   item = fused_items<T, 1, DROP>(a, shared, wave, item, 0, i1, 0);
   item = fused_items<T, 2, DROP>(a, shared, wave, item, i1, i2, n1);
   item = fused_items<T, 4, DROP>(a, shared, wave, item, i2, i4, n1 + n2);

@@ -87,3 +87,14 @@ def test_backward_stays_in_range_and_agrees(program, lengths, heads, used, thr, 
         for g in ("dq", "dk", "dv"):
             assert r[g]["bad"] == (0, 0) and r[g]["two"] <= tol and r[g]["double"] <= tol, (g, r[g])
         assert r["dv"]["two"] == 0 and (thr == 0 or r["dk"]["two"] == 0)
+
+
+@pytest.mark.parametrize("lengths,used", [([1] * 9, None), ([33, 40, 5, 70], None), ([69, 40], [33, 40]), ([300, 129], None)])
+def test_key_places_without_a_key_add_nothing(program, lengths, used):
+    """Every row attends to its sequence's last key alone, whose dP / (1 - p) = 524 288 is beyond f16's range, and half
+    the scores are dropped: dS = P (dP - D) is 0, kept or not.  What stands behind the last key is a copy of it with a mask
+    of its own, and its P (dP - D) would not be 0."""
+    r = emulate(program, "f16", 128, 2, lengths, used, values="last")
+    for g in ("dq", "dk", "dv"):
+        assert r[g]["bad"] == (0, 0) and r[g]["two"] == 0, (g, r[g])
+    assert r["dq"]["largest"] == 0 and r["dv"]["largest"] > 0

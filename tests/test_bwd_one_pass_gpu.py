@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import dropout_mask as dm
 from oracle import oracle
 from oracle.parity import G_TOL, gradient_errors
 from paper_2208_08124_amd import workloads as wl
@@ -115,3 +116,58 @@ def test_repeats_itself_and_leaves_the_statistics_of_the_two_passes():
     for x, y in zip(one, again):
         assert torch.equal(x, y)
     assert torch.equal(db.dk, two_dk)
+
+
+def test_key_places_without_a_key_add_nothing():
+    """The scores' gradients of a key that does not exist would overflow f16 (every row attends to its sequence's
+    last key alone, dP / (1 - p) = 524 288): all dS are 0, in the one pass as in the two."""
+    b = wl.make_batch(fill([1, 33, 40, 5, 70, 250], 240), 16, "f16", seed=3)
+    value = lambda x: wl.to_bits(np.array([x], np.float32), "f16")[0]
+    for name, x in (("q", 2.0), ("k", 0.0), ("v", 64.0), ("do", 64.0)):
+        b[name][:] = value(x)
+    b["k"][b["cu_seqlens"][1:] - 1] = value(4.0)
+    _, one, two = both_ways(b, (0.5, 99))
+    for x, y in zip(one, two):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
+    assert not one[0].any()
+
+
+def test_infinite_product_at_a_dropped_score():
+    """dO V^T overflows fp32 at one (query, key) pair that the mask drops: no gradient sees the infinity."""
+    n, drop = 70, (0.5, 4711)
+    b = wl.make_batch([n] + fill([64, 33, 120, 64], 250), 16, "bf16", seed=21)
+    keep = dm.keep_masks(np.array([0, n], np.int32), 16, *drop)[0][0]
+    q, k = next((q, k) for q in range(33, n - 1) for k in range(5, n) if not keep[q, k])
+    for name in ("v", "do"):
+        b[name][:n, 0, 0] = 0
+    huge = wl.to_bits(np.array([2e20], np.float32), "bf16")[0]
+    b["v"][k, 0, 0] = huge
+    b["do"][q, 0, 0] = huge
+    _, one, two = both_ways(b, drop)
+    assert all(torch.isfinite(x).all() for x in one)
+    compare(b, one, two, "bf16", drop)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_scaled_product_is_rounded_before_d_is_subtracted(dtype):
+    """Single-token sequences with P = 1, dO V^T = 1.5, 1/(1-p) = 4/3 in fp32 (1.33333337), D = 2, among longer ones: the
+    product rounds to 2 and a kept element's gradients are exactly zero; a dropped one has dS = -2."""
+    p, seed, h = 0.25, 12, 16
+    b = wl.make_batch(fill([1, 64, 1, 1], 800), h, dtype, seed=1)
+    one = lambda x: wl.to_bits(np.array([x], np.float32), dtype)[0]
+    for name, column, value in (("q", 1, 64.0), ("k", 0, 64.0), ("v", 0, 1.5), ("do", 0, 1.0)):
+        b[name][:] = 0
+        b[name][:, :, column] = one(value)
+    b["scale"] = 0.5
+    db = DeviceBatch(b, True)
+    db.o.zero_()
+    db.o[:, :, 0] = 2.0
+    db.lse.zero_()                    # the one score is q k = 0, so P = 1
+    db.bwd(dropout=(p, seed))
+    torch.cuda.synchronize()
+    rows = b["cu_seqlens"][:-1][b["lengths"] == 1]
+    keep = np.stack([dm.random_bytes(int(r), h, 1, 1, seed)[:, 0, 0] >= dm.threshold(p) for r in rows])
+    assert 0 < keep.sum() < keep.size
+    dq, dk = to_f64(db.dq)[rows], to_f64(db.dk)[rows]
+    assert np.array_equal(dq[:, :, 0], np.where(keep, 0.0, -64.0)) and (dq[:, :, 1:] == 0).all()
+    assert np.array_equal(dk[:, :, 1], np.where(keep, 0.0, -64.0)) and (dk[:, :, 0] == 0).all() and (dk[:, :, 2:] == 0).all()
