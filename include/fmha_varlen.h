@@ -190,6 +190,11 @@ int fmha_varlen_bwd_dropout(const fmha_varlen_params_t* p, const fmha_dropout_t*
                             const void* d_o, const float* lse, void* dq, void* dk, void* dv,
                             void* stream);
 
+/* How fmha_varlen_bwd (dropout null) or fmha_varlen_bwd_dropout would run with these arguments: 1 = one pass that
+ * forms the scores once, 2 = the two passes.  Reads host memory and the device's number of compute units only;
+ * -(an error code) if the arguments would be refused. */
+int32_t fmha_varlen_bwd_passes(const fmha_varlen_params_t* p, const fmha_dropout_t* dropout);
+
 /* Writes the keep mask itself, for tests and debugging: mask is device memory,
  * heads * total_tokens rows of row_bytes bytes (row_bytes >= the longest sequence,
  * and >= max_seqlen if that is given); byte k of row h * total_tokens + t becomes 1 if

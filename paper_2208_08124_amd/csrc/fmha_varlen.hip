@@ -59,8 +59,8 @@ struct Workspace {
 // Workgroups of the one-pass backward at most, and rows of fp32 dQ that each may be given.
 constexpr int64_t kFusedGrid = 256, kFusedSlabRows = 2048;
 
-// Workgroups of the one-pass backward: one per compute unit, a multiple of 8.
-int64_t fused_grid(int64_t items) { return ((items < kFusedGrid ? items : kFusedGrid) + 7) / 8 * 8; }
+// Workgroups of the one-pass backward for `items` items and at most `units` of them: a multiple of 8.
+int64_t fused_grid(int64_t items, int64_t units = kFusedGrid) { return ((items < units ? items : units) + 7) / 8 * 8; }
 
 Workspace carve(void* base, int64_t batch, int64_t total_tokens, int64_t heads) {
   Workspace w;
@@ -225,6 +225,9 @@ unsigned feed_grid(const fmha_varlen_params_t* p, int per_cu, const Workspace& w
   return (unsigned)g;
 }
 
+// Workgroups of the one-pass backward that run at a time: one per compute unit.
+int64_t fused_units() { return compute_units() < kFusedGrid ? compute_units() : kFusedGrid; }
+
 // Rows of fp32 dQ for each workgroup of the one-pass backward.
 // (a multiple of 256: the sweeps of a sequence that needs more begin at multiples of eight blocks)
 int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
@@ -234,48 +237,61 @@ int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
 }
 
 // Whether the backward runs as one pass (bwd_fused_kernel.h) or as two (bwd_kernels.h).  The figures are
-// two passes' time over one's, 16 heads unless stated, without / with dropout.
+// two passes' time over one's, without / with dropout, from 750 batches of 1 - 16 heads, 24 - 2048 tokens and lengths
+// equal, uniform, mostly long and mostly short, and 250 more with key counts of their own.
 //
-// The one pass is 1.15 - 1.5 / 1.1 - 1.8 times as fast while all compute units are busy, but its items are
+// The one pass is 1.1 - 1.5 / 1.1 - 1.8 times as fast while all compute units are busy, but its items are
 // whole sequences, where the two passes have tiles of 128 rows to deal out.  A compute unit's share of the
-// work is estimated from below by what the batch would be with all sequences as long.
+// work is estimated from below by what the batch would be with all sequences as long (in steps of 256 keys by 32
+// queries), and held against the longest sequence.
+//  - More rows than the fp32 dQ between sweeps has room for: the scores would be formed twice after all.
 //  - Up to 256 tokens (one sweep an item) it pays from a fifth of the longest sequence on: 0.98 / 0.99 at
-//    0.12 - 0.15, 1.04 - 1.14 / 1.06 - 1.19 at 0.2 - 0.5, even where a second round of items is nearly empty
-//    (272 equal items of 256 tokens: 1.07 / 1.17).
-//  - Longer sequences of mixed lengths: 0.98 - 1.01 / 0.95 - 1.02 at 0.36 - 0.48 of the longest, 1.06 - 1.16 / 1.12 - 1.17 at
-//    0.58 - 0.64 (one batch of 34, up to 1024 tokens, 0.81 / 1.02 at 0.67); above 1024 tokens, where there is less to be gained,
-//    0.95 - 0.98 / 0.86 - 0.90 at 0.60 - 0.64.  Where most are short the squares of the longer ones make the share
-//    larger than it is estimated here: 1.07 - 1.17 / 1.17 - 1.25 from 0.24 on (lengths of a fifth of the longest on average).
-//  - Longer ones that are (nearly) all equal take whole rounds: 0.83 - 0.91 / 0.82 - 0.87 where the rounds are
-//    0.56 - 0.69 full (0.95 / 0.85 for 160 items of 1024, but 1.10 / 1.18 for 160 of 512), 1.05 / 1.04 at 0.75.
-//    With few keys in a second sweep dropout costs more there than it saves: 272 ... 384 tokens 1.01 - 1.08 /
-//    0.94 - 0.97.
-// Sequences of up to 64 (128) tokens are taken four (two) heads at a time, and places without a head cost as
-// much as others.  Heads 1 / 2 / 3 / 5 / 6, without dropout: up to 64 tokens 0.47 / 0.87 / 1.09 / 0.89 / 1.02, up to 128
-// 0.6 / 0.96 / 0.92 / 0.95 / 1.0, up to 160 0.79 / 1.12 / 0.97, up to 256 1.0 / 1.17 / 0.94; with dropout (where an
-// empty place makes no mask) 0.6 / 1.1 / 1.4 / 1.16 / 1.34, 0.67 / 1.12 / 1.07 / 1.12 / 1.19, 0.92 / 1.21 / 1.07, 1.07 / 1.2 / 1.0.
+//    0.12 - 0.15, 1.04 - 1.5 / 1.06 - 1.7 from 0.2 on, even where a second round of items is nearly empty.
+//    Equal lengths of 65 - 80 leave a wavefront in four without a key: 0.93 - 0.97 / 0.97 - 1.09.
+//  - Longer sequences that are (nearly) all equal take whole rounds: 0.72 - 1.1 / 0.69 - 1.2 where the rounds are 0.5 - 0.65 full,
+//    0.96 - 1.4 / 0.92 - 1.3 from 0.7 on (0.93 - 1.0 / 0.86 - 1.06 above 1024 tokens at 0.79 - 0.88).  With few keys in a second sweep
+//    that sweep costs more than it saves: 257 - 320 tokens 0.85 - 1.03 / 0.85 - 1.0 in more than one round, with
+//    dropout 0.93 - 1.04 up to 416.
+//  - Longer sequences of mixed lengths: up to 512 tokens 0.8 - 1.2 / 0.7 - 1.1 at 0.2 - 0.4 of the longest, 0.97 - 1.0 / 0.96 - 1.02 at
+//    0.62 - 0.64, 1.0 - 1.2 / 0.98 - 1.12 from 0.65 on; up to 1024 one batch of 33 0.90 / 0.87 at 0.76 (another, of 34, 0.81 / 1.02 at
+//    0.67), 1.05 - 1.2 from 0.8 on; above, 0.95 - 1.02 / 0.86 - 0.95 at 0.5 - 0.64.  Where most are short the squares of the longer ones make
+//    the share larger than it is estimated here: 1.0 - 1.3 / 1.0 - 1.35 from 0.3 on up to 1024 tokens.
+//  - Sequences of up to 64 (128) tokens are taken four (two) heads at a time, and places without a head cost as
+//    much as others.  Heads 1 / 2 / 3 / 5 / 6, without dropout: up to 64 tokens 0.47 / 0.87 / 1.09 / 0.89 / 1.02, up to 128
+//    0.6 - 0.86 / 0.96 - 1.06 / 0.8 - 0.95 / 0.94 - 0.99 / 1.0, up to 160 0.79 / 1.12 / 0.97, up to 256 1.0 / 1.17 / 0.94; with dropout (where an
+//    empty place makes no mask) 0.6 / 1.1 / 1.4 / 1.16 / 1.34, 0.67 - 0.87 / 1.12 - 1.2 / 0.8 - 1.03 / 1.07 - 1.13 / 1.19, 0.92 / 1.21 / 1.07,
+//    1.07 / 1.2 / 1.0.  The length that counts is twice the mean where that is less than the longest.
+//  - With key counts of their own (seqused) all sequences are taken one head at a time, and the work goes by counts that the
+//    host does not know: rows of up to 64 tokens 0.44 - 0.75 / 0.54 - 0.83, up to 128 0.6 - 0.97 / 0.64 - 0.9, 129 - 256 1.0 - 1.4 / 0.98 - 1.37;
+//    longer ones in full rounds 0.96 - 1.5 / 0.98 - 1.4 from a share as large as the longest sequence on.
 bool one_pass(const fmha_varlen_params_t* p, const Workspace& w, bool dropout) {
   if (p->flags & (FMHA_FLAG_BWD_ONLY_DQ | FMHA_FLAG_BWD_ONLY_DKV)) return false;
-  const int n = p->max_seqlen, h = p->heads;
-  if (n <= 0) return false;
-  if (dropout) {
-    if (h == 1 && n <= 192) return false;
-  } else {
-    if (n <= 128 && h < 0.75 * ((h + 3) / 4 * 4)) return false;
-    if (n > 64 && n <= fmha::kFusedKeys && h < 0.8 * ((h + 1) / 2 * 2)) return false;
-  }
-  const size_t slab = (size_t)fused_grid((int64_t)p->batch * p->heads) * (size_t)fused_slab_rows(p) * fmha::kHeadDim * sizeof(float);
-  if (p->total_tokens > fmha::kFusedKeys && w.bytes_bwd - w.slab_off < slab) return false;
-  // in steps of 256 keys by 32 queries
+  const int64_t total = p->total_tokens;
+  const int h = p->heads, n = (int)(p->max_seqlen < total ? p->max_seqlen : total);
+  if (n <= 0 || p->batch <= 0 || n > kFusedSlabRows) return false;
+  const size_t slab = (size_t)fused_grid((int64_t)p->batch * h, fused_units()) * (size_t)fused_slab_rows(p) * fmha::kHeadDim * sizeof(float);
+  if (total > fmha::kFusedKeys && w.bytes_bwd - w.slab_off < slab) return false;
+  const int64_t units = fused_units(), items = (int64_t)p->batch * h, rounds = (items + units - 1) / units;
+  const double mean = (double)total / p->batch, full = (double)items / (double)(rounds * units);
   const double longest = (double)((n + 255) / 256) * ((n + 31) / 32);
-  const double share = (double)p->total_tokens * p->total_tokens * h / ((double)p->batch * 256 * 32 * kFusedGrid);
-  if (n <= fmha::kFusedKeys) return share >= 0.2 * longest;
-  if (p->total_tokens >= 0.9 * n * p->batch) {
-    const int64_t items = (int64_t)p->batch * h, rounds = (items + kFusedGrid - 1) / kFusedGrid;
-    return items >= 0.7 * (double)(rounds * kFusedGrid) && !(dropout && n <= 416);
+  const double share = (double)total * mean * h / (256. * 32. * (double)units) / longest;
+  if (p->seqused) return mean > 128 && (n <= fmha::kFusedKeys ? share >= 0.2 : share >= 1. && full >= 0.85);
+  const double len = 2 * mean < n ? 2 * mean : n;
+  if (dropout) {
+    if (h == 1 && len <= 192) return false;
+    if (h == 3 && len > 64 && len <= 128) return false;
+  } else {
+    if (len <= 128 && h < 0.75 * ((h + 3) / 4 * 4)) return false;
+    if (len > 64 && len <= fmha::kFusedKeys && h < 0.8 * ((h + 1) / 2 * 2)) return false;
   }
-  if (n > 1024) return share >= 0.9 * longest;
-  return share >= (p->total_tokens < 0.3 * n * p->batch ? 0.3 : 0.6) * longest;
+  const bool equal = mean >= 0.9 * n;
+  if (n <= fmha::kFusedKeys) return share >= 0.2 && !(equal && !dropout && n > 64 && n <= 80);
+  if (equal) {
+    if (dropout ? n <= 416 : n <= 320 && rounds > 1) return false;
+    return full >= (n > 1024 ? 0.85 : dropout ? 0.75 : 0.7);
+  }
+  if (n <= 1024 && mean < 0.3 * n) return share >= 0.3;
+  return share >= (n <= 512 ? 0.65 : n <= 1024 ? 0.8 : 0.9);
 }
 
 // Dropout arguments for the kernels; d == nullptr means no dropout.
@@ -389,6 +405,15 @@ int fmha_varlen_bwd_dropout(const fmha_varlen_params_t* p, const fmha_dropout_t*
                             const void* k, const void* v, const void* o, const void* d_o,
                             const float* lse, void* dq, void* dk, void* dv, void* stream) {
   return run_bwd(p, dropout, true, q, k, v, o, d_o, lse, dq, dk, dv, stream);
+}
+
+int32_t fmha_varlen_bwd_passes(const fmha_varlen_params_t* p, const fmha_dropout_t* dropout) {
+  int rc = check_common(p, true);
+  if (rc) return -rc;
+  fmha::DropArgs da;
+  if ((rc = drop_args(dropout, false, &da))) return -rc;
+  g_err[0] = 0;
+  return one_pass(p, carve(p->workspace, p->batch, p->total_tokens, p->heads), da.thr != 0) ? 1 : 2;
 }
 
 int fmha_dropout_keep_mask(const fmha_varlen_params_t* p, const fmha_dropout_t* dropout, int32_t orientation,
@@ -529,7 +554,7 @@ int run_bwd(const fmha_varlen_params_t* p, const fmha_dropout_t* d, bool with_dr
   a.dk = static_cast<uint16_t*>(dk);
   a.dv = static_cast<uint16_t*>(dv);
   if (one_pass(p, w, da.thr != 0)) {
-    const int64_t grid = fused_grid((int64_t)p->batch * p->heads);
+    const int64_t grid = fused_grid((int64_t)p->batch * p->heads, fused_units());
     a.seqs = w.seqs;
     a.slab = w.slab;
     a.slab_rows = fused_slab_rows(p);

@@ -25,7 +25,7 @@ FMHA_EMB_NO_DIE_SPLIT = 4
 
 EXPORTS = ("fmha_varlen_workspace_size", "fmha_varlen_fwd", "fmha_varlen_bwd",
            "fmha_varlen_fwd_static", "fmha_varlen_static_scratch_bytes",
-           "fmha_varlen_fwd_dropout", "fmha_varlen_bwd_dropout", "fmha_dropout_keep_mask",
+           "fmha_varlen_fwd_dropout", "fmha_varlen_bwd_dropout", "fmha_varlen_bwd_passes", "fmha_dropout_keep_mask",
            "fmha_unpad_indices_host", "fmha_unpad_indices", "fmha_gather_rows", "fmha_scatter_rows",
            "fmha_dropout_add_ln_fwd", "fmha_dropout_add_ln_bwd", "fmha_dropout_add_ln_bwd_workspace_size",
            "fmha_embedding_bwd", "fmha_embedding_sort_workspace_size", "fmha_embedding_sort",
@@ -94,6 +94,8 @@ def lib():
         L.fmha_varlen_fwd_dropout.restype = ctypes.c_int
         L.fmha_varlen_bwd_dropout.argtypes = [ctypes.POINTER(Params), dp] + [vp] * 10
         L.fmha_varlen_bwd_dropout.restype = ctypes.c_int
+        L.fmha_varlen_bwd_passes.argtypes = [ctypes.POINTER(Params), dp]
+        L.fmha_varlen_bwd_passes.restype = ctypes.c_int32
         L.fmha_dropout_keep_mask.argtypes = [ctypes.POINTER(Params), dp, ctypes.c_int32, ctypes.c_int32, vp, vp]
         L.fmha_dropout_keep_mask.restype = ctypes.c_int
         i32 = ctypes.c_int32
@@ -249,6 +251,23 @@ def fmha_varlen_bwd(q, k, v, o, d_o, lse, cu_seqlens, max_seqlen, scale, dq, dk,
         d = _dropout(dropout)
         _check(lib().fmha_varlen_bwd_dropout(ctypes.byref(p), ctypes.byref(d), *ptrs))
     del keep
+
+
+def fmha_varlen_bwd_passes(batch, total_tokens, heads, max_seqlen, *, dropout=None, seqused=False, only=None,
+                           workspace_bytes=None):
+    """1 or 2: how fmha_varlen_bwd runs on a batch of this shape (with a workspace of the size that
+    fmha_varlen_workspace_size gives, or of `workspace_bytes`).  Needs no GPU: nothing is read but the sizes."""
+    p = Params()
+    p.batch, p.total_tokens, p.heads, p.head_dim, p.max_seqlen = batch, total_tokens, heads, 64, int(max_seqlen)
+    p.dtype, p.scale = FMHA_F16, 1.0
+    p.flags = {None: 0, "dq": FMHA_FLAG_BWD_ONLY_DQ, "dkv": FMHA_FLAG_BWD_ONLY_DKV}[only]
+    p.cu_seqlens = p.workspace = 256            # (never dereferenced on the host)
+    p.seqused = 256 if seqused else None
+    p.workspace_bytes = (fmha_varlen_workspace_size(batch, total_tokens, heads, True) if workspace_bytes is None
+                         else workspace_bytes)
+    rc = lib().fmha_varlen_bwd_passes(ctypes.byref(p), ctypes.byref(_dropout(dropout)) if dropout else None)
+    _check(-rc if rc < 0 else FMHA_OK)
+    return rc
 
 
 def fmha_dropout_keep_mask(heads, cu_seqlens, max_seqlen, dropout, mask, workspace, *, orientation=0,

@@ -15,6 +15,7 @@ import torch
 from oracle import dropout_mask as dm
 from oracle import oracle
 from oracle.parity import G_TOL, gradient_errors
+from paper_2208_08124_amd import fmha
 from paper_2208_08124_amd import workloads as wl
 
 from gpu_util import DeviceBatch, oracle_inputs, to_f64
@@ -31,12 +32,14 @@ def fill(some, n):
 
 def both_ways(b, dropout=None):
     """dQ, dK, dV by one call and by the two passes."""
-    # the batch is one the library takes the kernel for: a compute unit's share of the work (in blocks of
+    # the batch is one the library takes the kernel for, with some room: a compute unit's share of the work (in blocks of
     # 256 keys by 32 queries, as if all sequences were as long) is at least 0.6 of the longest sequence's
-    # (0.2 up to 256 tokens, 0.9 beyond 1024); lengths are mixed, or all equal and items in whole rounds
+    # (0.2 up to 256 tokens, 0.9 beyond 1024)
     n = b["max_seqlen"]
     share = b["total_tokens"] ** 2 * b["heads"] / (b["batch"] * 8192.0 * 256)
     assert share >= (0.2 if n <= 256 else 0.6 if n <= 1024 else 0.9) * -(-n // 256) * -(-n // 32)
+    assert fmha.fmha_varlen_bwd_passes(b["batch"], b["total_tokens"], b["heads"], n, dropout=dropout,
+                                       seqused="seqused" in b) == 1
     db = DeviceBatch(b, True)
     db.fwd(dropout=dropout)
     for x in (db.dq, db.dk, db.dv):
@@ -171,3 +174,44 @@ def test_scaled_product_is_rounded_before_d_is_subtracted(dtype):
     dq, dk = to_f64(db.dq)[rows], to_f64(db.dk)[rows]
     assert np.array_equal(dq[:, :, 0], np.where(keep, 0.0, -64.0)) and (dq[:, :, 1:] == 0).all()
     assert np.array_equal(dk[:, :, 1], np.where(keep, 0.0, -64.0)) and (dk[:, :, 0] == 0).all() and (dk[:, :, 2:] == 0).all()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("batch,length,heads,dropout", [
+    (16, 2048, 16, None),            # eight sweeps, and the whole of the buffer for dQ between them
+    (48, 512, 16, (0.1, 5)),
+    (64, 512, 4, None),              # one item for every workgroup
+])
+def test_equal_lengths(batch, length, heads, dropout, dtype):
+    b = wl.make_batch([length] * batch, heads, dtype, seed=length)
+    _, one, two = both_ways(b, dropout)
+    compare(b, one, two, dtype, dropout)
+    if dropout is None:              # one sequence, two heads of it
+        rows = slice(length, 2 * length)
+        x = {n: v[rows, :2] for n, v in oracle_inputs(b).items() if n in ("q", "k", "v", "do")}
+        cu = wl.cu_from_lengths(np.array([length]))
+        for name, got, want in zip(("dq", "dk", "dv"), one, oracle.bwd(x["q"], x["k"], x["v"], x["do"], cu, b["scale"])):
+            rel, fro = gradient_errors(to_f64(got[rows, :2]), want, cu)
+            assert rel <= G_TOL and fro <= G_TOL, f"{name}: {rel:.3e} {fro:.3e}"
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("lengths,heads,dropout", [
+    ([2100, 4096, 2049], 16, None),   # keep the two passes: more rows than the buffer for dQ between sweeps holds
+    ([2100, 2300], 16, (0.1, 3)),
+])
+def test_more_rows_than_the_buffer_holds(lengths, heads, dropout, dtype):
+    """Against the one pass, which a longest sequence stated too small (512) sends the same batch to."""
+    b = wl.make_batch(fill(lengths, 12), heads, dtype, seed=5)
+    db = DeviceBatch(b, True)
+    assert fmha.fmha_varlen_bwd_passes(b["batch"], b["total_tokens"], heads, b["max_seqlen"], dropout=dropout) == 2
+    db.fwd(dropout=dropout)
+    db.bwd(reuse_schedule=True, dropout=dropout)
+    two = [x.clone() for x in (db.dq, db.dk, db.dv)]
+    b["max_seqlen"] = 512
+    assert fmha.fmha_varlen_bwd_passes(b["batch"], b["total_tokens"], heads, 512, dropout=dropout) == 1
+    for x in (db.dq, db.dk, db.dv):
+        x.fill_(float("nan"))
+    db.bwd(reuse_schedule=True, dropout=dropout)
+    torch.cuda.synchronize()
+    compare(b, [db.dq, db.dk, db.dv], two, dtype, dropout)
