@@ -59,7 +59,7 @@ typedef enum {
   FMHA_OK = 0,
   FMHA_ERR_INVALID_ARG = 1, /* null / misaligned pointer, bad size, bad stride, bad prefix sums */
   FMHA_ERR_UNSUPPORTED = 2, /* head_dim != 64, unknown dtype */
-  FMHA_ERR_WORKSPACE = 3,   /* workspace missing or smaller than fmha_varlen_workspace_size() */
+  FMHA_ERR_WORKSPACE = 3,   /* workspace missing or too small, see fmha_varlen_workspace_size() */
   FMHA_ERR_HIP = 4          /* a HIP launch failed */
 } fmha_status_t;
 
@@ -109,7 +109,10 @@ typedef struct fmha_varlen_params {
 /* Bytes of device workspace for a batch of this shape (tile list, list of sequences; plus, if
  * need_bwd, two fp32 per (token, head): the row sums of dO o O and the
  * log-sum-exp in base-2 units, and fp32 dQ of the sequences under way: up to 2048 rows of 256
- * bytes for each of at most 256 workgroups, 128 MiB, none for batches of up to 256 tokens).  Pure host arithmetic; returns 0 on invalid sizes. */
+ * bytes for each of at most 256 workgroups, 128 MiB, none for batches of up to 256 tokens).  The
+ * backward also takes a workspace without that last part, i.e. of fmha_varlen_workspace_size(.., 0) + 2 x 4 (T H + 1)
+ * bytes, each of the two rounded up to 256; it then runs as the two passes, which use no more: enough for an
+ * unknown max_seqlen and for halves called by themselves.  Pure host arithmetic; returns 0 on invalid sizes. */
 size_t fmha_varlen_workspace_size(int32_t batch, int32_t total_tokens, int32_t heads,
                                   int32_t need_bwd);
 

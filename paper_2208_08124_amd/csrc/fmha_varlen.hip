@@ -133,8 +133,9 @@ int check_common(const fmha_varlen_params_t* p, bool bwd, bool list_only = false
     if (cu[p->batch] != p->total_tokens)
       return fail(FMHA_ERR_INVALID_ARG, "cu_seqlens_host[batch]=%d differs from total_tokens=%d", cu[p->batch], p->total_tokens);
   }
+  // (a backward without room for fp32 dQ between sweeps takes the two passes, which use none)
   const Workspace sizes = carve(nullptr, p->batch, p->total_tokens, p->heads);
-  const size_t need = list_only ? sizes.bytes_list : bwd ? sizes.bytes_bwd : sizes.bytes_fwd;
+  const size_t need = list_only ? sizes.bytes_list : bwd ? sizes.slab_off : sizes.bytes_fwd;
   if (!p->workspace) return fail(FMHA_ERR_WORKSPACE, "workspace is null (%zu bytes needed)", need);
   if (misaligned(p->workspace, kAlign)) return fail(FMHA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (p->workspace_bytes < need) return fail(FMHA_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", p->workspace_bytes, need);
@@ -245,6 +246,7 @@ int32_t fused_slab_rows(const fmha_varlen_params_t* p) {
 // work is estimated from below by what the batch would be with all sequences as long (in steps of 256 keys by 32
 // queries), and held against the longest sequence.
 //  - More rows than the fp32 dQ between sweeps has room for: the scores would be formed twice after all.
+//    Nor without that room in the workspace, whatever the lengths (the longest may have been stated too small).
 //  - Up to 256 tokens (one sweep an item) it pays from a fifth of the longest sequence on: 0.98 / 0.99 at
 //    0.12 - 0.15, 1.04 - 1.5 / 1.06 - 1.7 from 0.2 on, even where a second round of items is nearly empty.
 //    Equal lengths of 65 - 80 leave a wavefront in four without a key: 0.93 - 0.97 / 0.97 - 1.09.
@@ -270,7 +272,8 @@ bool one_pass(const fmha_varlen_params_t* p, const Workspace& w, bool dropout) {
   const int h = p->heads, n = (int)(p->max_seqlen < total ? p->max_seqlen : total);
   if (n <= 0 || p->batch <= 0 || n > kFusedSlabRows) return false;
   const size_t slab = (size_t)fused_grid((int64_t)p->batch * h, fused_units()) * (size_t)fused_slab_rows(p) * fmha::kHeadDim * sizeof(float);
-  if (total > fmha::kFusedKeys && w.bytes_bwd - w.slab_off < slab) return false;
+  const size_t given = p->workspace_bytes < w.bytes_bwd ? p->workspace_bytes : w.bytes_bwd;
+  if (total > fmha::kFusedKeys && given - w.slab_off < slab) return false;
   const int64_t units = fused_units(), items = (int64_t)p->batch * h, rounds = (items + units - 1) / units;
   const double mean = (double)total / p->batch, full = (double)items / (double)(rounds * units);
   const double longest = (double)((n + 255) / 256) * ((n + 31) / 32);

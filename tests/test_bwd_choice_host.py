@@ -55,3 +55,24 @@ def test_halves_by_themselves_and_an_unknown_longest_sequence_take_two():
         passes(256, 512, 16, 512, dropout=(1.5, 0))
     with pytest.raises(fmha.FmhaError):
         passes(256, 512, 16, 512, workspace_bytes=4096)
+
+
+def without_dq_buffer(batch, total_tokens, heads):
+    stats = (4 * (total_tokens * heads + 1) + 255) // 256 * 256
+    return fmha.fmha_varlen_workspace_size(batch, total_tokens, heads, False) + 2 * stats
+
+
+@pytest.mark.parametrize("batch,mean,heads,longest", [(56, 281, 16, 512), (256, 200, 16, 256), (16, 2048, 16, 2048),
+                                                      (3, 20, 5, 64)])
+def test_workspace_without_the_buffer_for_dq(batch, mean, heads, longest):
+    """The two passes use no fp32 dQ between sweeps: they run in a workspace without it."""
+    least, full = without_dq_buffer(batch, batch * mean, heads), fmha.fmha_varlen_workspace_size(batch, batch * mean, heads, True)
+    want = passes(batch, mean, heads, longest)
+    assert passes(batch, mean, heads, longest, workspace_bytes=full) == want
+    assert passes(batch, mean, heads, longest, workspace_bytes=full + (1 << 30)) == want
+    assert passes(batch, mean, heads, longest, workspace_bytes=least) == 2
+    for kw in (dict(only="dq"), dict(only="dkv"), dict(dropout=DROP)):
+        assert passes(batch, mean, heads, longest, workspace_bytes=least, **kw) == 2
+    assert passes(batch, mean, heads, 0, workspace_bytes=least) == 2
+    with pytest.raises(fmha.FmhaError):
+        passes(batch, mean, heads, longest, workspace_bytes=least - 1)

@@ -215,3 +215,22 @@ def test_more_rows_than_the_buffer_holds(lengths, heads, dropout, dtype):
     db.bwd(reuse_schedule=True, dropout=dropout)
     torch.cuda.synchronize()
     compare(b, [db.dq, db.dk, db.dv], two, dtype, dropout)
+
+
+@pytest.mark.parametrize("dropout", [None, (0.1, 5)])
+def test_workspace_without_the_buffer_for_dq(dropout):
+    """A backward in the smallest workspace runs as the two passes do, and writes nothing behind it."""
+    b = wl.make_batch(fill(LONG, 110), 16, "f16", seed=6)
+    db, _, two = both_ways(b, dropout)
+    two = [x.clone() for x in two]
+    t = b["total_tokens"]
+    least = fmha.fmha_varlen_workspace_size(b["batch"], t, 16, False) + 2 * ((4 * (t * 16 + 1) + 255) // 256 * 256)
+    whole = db.ws
+    whole.fill_(0x5A)
+    db.ws = whole[:least]
+    for x in (db.dq, db.dk, db.dv):
+        x.fill_(float("nan"))
+    db.bwd(dropout=dropout)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip((db.dq, db.dk, db.dv), two))
+    assert (whole[least:] == 0x5A).all()
