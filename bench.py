@@ -153,7 +153,7 @@ def main():
 
         def step(self):
             self.fwd()      # builds the tile list, then the forward kernel
-            self.bwd()      # reuses the list: dQ pass + dK/dV pass
+            self.bwd()      # reuses the list: one pass over the scores, or two
 
     def precondition(fn, seconds=0.5):
         """Untimed steps for a fixed duration ahead of a timed region: a short run (the driver's
@@ -208,7 +208,11 @@ def main():
     def kernel_times(steps):
         # the plain forward and the one with dropout are different kernels
         fwd_name = "fmha_fwd64_kernel" if Dev.drop is None else "fmha_fwd_kernel"
-        legs = [(fwd_name, lambda x: x.fwd(reuse=True)), ("bwd_fused_kernel", lambda x: x.bwd())]
+        legs = [(fwd_name, lambda x: x.fwd(reuse=True))]
+        if fmha.fmha_varlen_bwd_passes(b["batch"], T, H, b["max_seqlen"], dropout=Dev.drop, seqused="seqused" in b) == 1:
+            legs.append(("bwd_fused_kernel", lambda x: x.bwd()))
+        else:
+            legs += [("bwd_dq_kernel", lambda x: x.bwd(only="dq")), ("bwd_dkv_kernel", lambda x: x.bwd(only="dkv"))]
         evs = [[torch.cuda.Event(enable_timing=True) for _ in range(len(legs) + 1)] for _ in range(steps)]
         for i in range(n_sets):
             sets[i].step()
@@ -267,13 +271,14 @@ def main():
                         "value": round(fl_all / dsec / 1e12, 3),
                         "kernels_ms": {k: round(v, 5) for k, v in dk_ms.items()}}
     del sets
-    k_fl = {"fmha_fwd_kernel": fl_fwd, "fmha_fwd64_kernel": fl_fwd, "bwd_fused_kernel": fl_dq + fl_dkv}
+    k_fl = {"fmha_fwd_kernel": fl_fwd, "fmha_fwd64_kernel": fl_fwd, "bwd_fused_kernel": fl_dq + fl_dkv,
+            "bwd_dq_kernel": fl_dq, "bwd_dkv_kernel": fl_dkv}
     dom = max(k_ms, key=k_ms.get)
     ach = k_fl[dom] / (k_ms[dom] * 1e-3) / 1e12
     peak = PEAK_TFLOPS[dt]
     roofline = {"bound": "mfma", "kernel": dom, "achieved": round(ach, 2), "peak": peak,
                 "unit": "TFLOP/s", "frac": round(ach / peak, 4),
-                "traffic": None if args.uniform else stored_traffic(b["name"], dom),
+                "traffic": None if args.uniform else stored_traffic(b["name"], dom + (" (dropout)" if args.dropout > 0 else "")),
                 "avg_launch_ms": round(k_ms[dom], 5),
                 "kernels_ms": {k: round(v, 5) for k, v in k_ms.items()},
                 "kernels_tflops": {k: round(k_fl[k] / (k_ms[k] * 1e-3) / 1e12, 2) for k in k_ms},

@@ -49,6 +49,23 @@ def test_default_line_has_the_agreed_fields():
     assert abs(d["value"] - d["useful_flop_per_step"] / (d["ms_per_step"] * 1e-3) / 1e12) < 0.01 * d["value"]
 
 
+@pytest.mark.parametrize("uniform,backward", [
+    ("512,32", ["bwd_fused_kernel"]),
+    ("600,4", ["bwd_dq_kernel", "bwd_dkv_kernel"]),   # 64 items: too few for the one pass
+])
+def test_the_backward_is_reported_under_the_kernels_that_ran(uniform, backward):
+    d = run_bench("--uniform", uniform, "--steps", "5", "--warmup", "1", "--no-cpu-baseline", "--no-padded")
+    r = d["roofline"]
+    assert sorted(r["kernels_ms"]) == sorted(["fmha_fwd64_kernel"] + backward) and r["kernel"] in r["kernels_ms"]
+
+
+def test_the_traffic_with_dropout_is_that_of_its_own_instances():
+    d = run_bench("--dropout", "0.1", "--steps", "5", "--warmup", "1", "--no-cpu-baseline", "--no-padded")
+    with open(os.path.join(ROOT, "profiles", "traffic.json")) as fh:
+        k = json.load(fh)["kernels"][d["roofline"]["kernel"] + " (dropout)"]
+    assert d["roofline"]["traffic"] == k["fetch_bytes"] + k["write_bytes"]
+
+
 @pytest.mark.parametrize("op,bound", [("unpad", "hbm"), ("layernorm", "hbm"), ("embedding", "hbm")])
 def test_other_modes_print_one_line(op, bound):
     d = run_bench("--op", op, "--steps", "5", "--warmup", "1")
