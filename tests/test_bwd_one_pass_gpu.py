@@ -135,6 +135,24 @@ def test_key_places_without_a_key_add_nothing():
     assert not one[0].any()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_single_token_sequences(dtype):
+    """P = 1 and O = V, so dP = D and dQ = dK = 0 but for rounding.  Products of 16-bit numbers are exact in fp32; with
+    S = sum_c |dO_c V_c|, D takes at most 8 roundings of sums up to S and dP - D, summed from -D on, at most 64 of sums
+    up to 2 S (truncated, 2^-23, if the matrix cores do): |dS| <= 2^-16 S.  dS and the result are rounded to 16 bits."""
+    b = wl.make_batch(fill([1, 64, 33, 1, 200], 300), 16, dtype, seed=8)
+    db, one, two = both_ways(b)
+    compare(b, one, two, dtype)
+    rows = b["cu_seqlens"][:-1][b["lengths"] == 1]
+    x = {n: v[rows] for n, v in oracle_inputs(b).items()}
+    o, dq, dk, dv = (to_f64(t)[rows] for t in [db.o] + one)
+    assert np.array_equal(o, x["v"]) and np.array_equal(dv, x["do"])
+    tiny = 2.0 ** -25 if dtype == "f16" else 0.0                        # half the smallest f16
+    ds = 2.0 ** -16 * np.abs(x["do"] * x["v"]).sum(axis=2, keepdims=True) * (1 + 2.0 ** -7) + tiny
+    for got, with_ in ((dq, x["k"]), (dk, x["q"])):
+        assert (np.abs(got) <= b["scale"] * ds * np.abs(with_) * (1 + 2.0 ** -8) + tiny).all()
+
+
 def test_infinite_product_at_a_dropped_score():
     """dO V^T overflows fp32 at one (query, key) pair that the mask drops: no gradient sees the infinity."""
     n, drop = 70, (0.5, 4711)
