@@ -72,7 +72,7 @@ typedef enum { FMHA_F16 = 0, FMHA_BF16 = 1 } fmha_dtype_t;
 #define FMHA_FLAG_REUSE_SCHEDULE 1u
 /* fmha_varlen_bwd only: run one half of the backward as a pass by itself.  (With neither flag
  * the library takes one pass that forms the scores once, or both of these, by the sizes of
- * the batch; either way the statistics are left behind.)  The dQ pass also
+ * the batch and of the workspace; either way the statistics are left behind.)  The dQ pass also
  * writes the per-row statistics into the workspace; the dK/dV pass reads them,
  * so a dK/dV-only call must follow a dQ pass (or a whole backward) on the same workspace and inputs.
  * (The statistics depend on o, d_o and lse alone: the two passes may be given

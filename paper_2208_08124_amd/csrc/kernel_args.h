@@ -64,14 +64,14 @@ struct BwdArgs {
   FeedArgs feed;
   const uint16_t *q, *k, *v, *o, *d_o;
   const float* lse;  // [H, T]
-  float* dsum;       // [H, T] -rowsum(dO o O), workspace (written by the dQ pass)
-  float* lse2;       // [H, T] lse * log2(e), workspace (written by the dQ pass)
+  float* dsum;       // [H, T] -rowsum(dO o O), workspace (written by the one-pass backward or the dQ pass)
+  float* lse2;       // [H, T] lse * log2(e), workspace (written by the same)
   uint16_t *dq, *dk, *dv;
   int64_t q_stride, k_stride, v_stride, o_stride, do_stride, dq_stride, dk_stride, dv_stride;
   // one-pass backward (bwd_fused_kernel.h)
   const TileItem* seqs;  // sequences (row0 unused), those of one head at a time first, then two, then four
   float* slab;           // fp32 dQ on its way from sweep to sweep: slab_rows rows of 64 per workgroup
-  int32_t slab_rows;     // a multiple of 32
+  int32_t slab_rows;     // a multiple of 256: what is swept at a time begins at a multiple of eight blocks of 32
 };
 
 // The tile list and its count were written by an earlier kernel and are only

@@ -9,7 +9,10 @@
 namespace fmha {
 
 constexpr int kSchedThreads = 1024;
-constexpr int kSchedBuckets = 128;  // bucket = ceil(keys / 8), clipped; bucket 0 = longest
+// bucket = ceil(keys / 8), clipped; bucket 0 = longest.  (More than 1016 keys are one bucket, in the order in which its
+// places are drawn.  Tiles do not mind; the one-pass backward's items are whole sequences, and batches that mix such lengths
+// have to bring it more work for each compute unit: the last threshold of one_pass().)
+constexpr int kSchedBuckets = 128;
 
 __device__ __forceinline__ int sched_bucket(int nkeys) {
   int b = (nkeys + 7) >> 3;
